@@ -43,7 +43,7 @@ WORKLOADS = {
           "Chebyshev degree 16, 12th-order FD, Gamma, spin-unpolarised",
     "c1": "6-atom TiO2-like cell, 8.7x8.7x5.6 bohr, grid 36x36x24, 32 states, Chebyshev degree 20",
     "c2k": "c2 cell spin-polarised with the shifted 2x2x2 k-point set: 16 complex (spin, k) blocks of "
-           "497664 x 256 in one context, one persistent stencil launch per Chebyshev step over all of them",
+           "497664 x 256 in one context, one stencil launch per Chebyshev step over all of them",
 }
 
 
@@ -207,7 +207,7 @@ def bench_scf_compare(args):
 def bench_batch(args):
     """Sixteen independent cells (4 each of 6, 12, 24 and 48 atoms), FP64,
     degree 16: a step is one ChFSI pass (filter + Rayleigh-Ritz) on every
-    cell.  Timed batched (one persistent stencil launch per Chebyshev step
+    cell.  Timed batched (one stencil launch per Chebyshev step
     over all 16 blocks) and sequential (each cell's own launches)."""
     import torch
     import workloads
@@ -278,13 +278,13 @@ def main():
                     help="run one plain 1 GiB device copy first (calibrates hardware byte counters)")
     ap.add_argument("--tile", default=None,
                     help="stencil tile shape TX,TYt,RY,TZ[,ring] (skips the autotuner, e.g. for profiling; "
-                         "ring: halo rows read with the queue head)")
+                         "ring: accepted, no effect)")
     ap.add_argument("--scf-compare", action="store_true",
                     help="SCF wall time on held-out 24-atom cells: mixed precision with the learned start against "
                          "FP64 with the isolated-atom start (needs the trained site network)")
     ap.add_argument("--cells", type=int, default=8, help="cells for --scf-compare")
     ap.add_argument("--batch", action="store_true",
-                    help="measure the 16-cell batched workload instead (one persistent stencil launch per "
+                    help="measure the 16-cell batched workload instead (one stencil launch per "
                          "Chebyshev step over all cells) against the same cells run one after another")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -468,8 +468,7 @@ def measure(args, config, precision, hcu, torch, top):
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic("k_stencil", config, prec, tile, ("stencil.hip",)),
-                "kernel": ("k_stencil_batch (persistent, all (spin, k) blocks)" if nsk > 1 else
-                           "k_stencil_big" if tuning["tile_x"] * tuning["tile_yt"] > 512 else "k_stencil")
+                "kernel": ("k_stencil_multi (all (spin, k) blocks)" if nsk > 1 else "k_stencil")
                           + " (12th-order FD stencil + V_loc + Chebyshev three-term step)",
                 "avg_launch_ms": round(st_ms, 4), "algorithmic_bytes_per_launch": int(bytes_launch),
                 "tile": tile}

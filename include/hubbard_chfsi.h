@@ -379,14 +379,15 @@ hcu_status hcu_hubbard_stress(hcu_ctx* ctx, const double* occ, double* stress);
  * launch (autotune output). */
 typedef struct hcu_tuning {
   int tile_x, tile_yt, ry, tile_z;
-  int halo_ring;   /* 1: the y/x halo of a plane is read together with the
-                      tile's own queue head, R planes before the plane is
-                      computed, and held in an LDS ring of R planes (order-12
+  int halo_ring;   /* 0 or 1, admitted with 1 as before for the order-12
                       stencil, at most 4 halo values per thread and 512
-                      threads, LDS within 160 KB) */
+                      threads, and LDS for R planes of halo within 160 KB.
+                      Asked for the halo of a plane to be read together with
+                      the tile's own rows of it; every shape does so now, so
+                      the flag changes nothing */
   double stencil_ms;
 } hcu_tuning;
-/* Time every admissible tile shape (with and without the halo ring) on the
+/* Time every admissible tile shape on the
  * full orbital block of (spin 0, k 0) (contents are not changed) and keep
  * the fastest; shapes the device cannot launch are skipped.  tile_x = 0 in
  * hcu_set_tuning restores the built-in choice.  Errors: HCU_INVALID_ARG for
@@ -436,8 +437,8 @@ hcu_status hcu_load_state(hcu_ctx* ctx, const void* host, size_t bytes);
 /* ---------------------------------------------------------------- batches
  * Independent problems (cells of different size, each with its spins and
  * k-points) advanced together: in every Chebyshev step the stencil of every
- * (cell, spin, k) block runs as ONE persistent launch that drains a work list
- * of (block, tile, z-chunk, state) items; projections, scatters and the
+ * (cell, spin, k) block runs as ONE launch over the (block, tile, z-chunk,
+ * state) items of all blocks (one launch per tile shape); projections, scatters and the
  * Rayleigh-Ritz steps run per block.  Members must be bound to the same
  * stream and share the block element type (precision, real/complex), the
  * filter degree and n0.  A batch does not own its contexts. */

@@ -35,13 +35,17 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"),
 ]
-SOURCES = ["setup.hip", "stencil.hip", "nonlocal.hip", "proj.hip", "gemm.hip", "scf_kernels.hip", "mlp.hip", "state.hip",
-           "noalloc.hip", "forces.hip", "hxc.hip", "eig.hip", "api.hip"]
+# (source, object, extra flags); the stencil is compiled once per element type
+SOURCES = [("stencil.hip", f"stencil_{t}", [f"-DHCU_STENCIL_ELEM={i}"])
+           for i, t in enumerate(("f64", "f32", "c128", "c64"))]
+SOURCES += [(f"{s}.hip", s, []) for s in ("setup", "nonlocal", "proj", "gemm", "scf_kernels", "mlp", "state", "noalloc",
+                                          "forces", "hxc", "eig", "api")]
 
 
-def _compile(src, sanitize=False):
-    obj = os.path.join(OBJ_DIR_SAN if sanitize else OBJ_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, *(SAN_FLAGS if sanitize else []), "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit, sanitize=False):
+    src, name, extra = unit
+    obj = os.path.join(OBJ_DIR_SAN if sanitize else OBJ_DIR, name + ".o")
+    cmd = [HIPCC, *FLAGS, *extra, *(SAN_FLAGS if sanitize else []), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")

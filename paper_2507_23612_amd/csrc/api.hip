@@ -37,7 +37,6 @@ size_t esize(const Ctx& c) { return (c.mixed ? 4 : 8) * (c.any_complex ? 2 : 1);
 
 constexpr int kInfoPerBlock = 4;   // eigensolve status words per (spin, k): Cholesky, eigensolver, guard
 constexpr size_t kBatchJobBytes = 1 << 20;   // stencil job records of one batched pass (~2900 jobs)
-constexpr unsigned long long kPersistentMinItems = 4096;   // smaller batched launches use one workgroup per item
 
 // Workspace layout.  Buffers whose size does not depend on the atom
 // positions come first (orbitals, work blocks, small dense buffers), then the
@@ -76,7 +75,6 @@ size_t layout(Ctx& c, char* base, bool assign = true) {
     c.d_X = X; c.d_v0 = v0; c.d_PX = PX; c.d_W = W; c.d_P = P; c.d_Q = Q; c.d_PY = PY;
   }
   b.take(c.d_jobs, kBatchJobBytes);
-  b.take(c.d_counters, sizeof(unsigned long long) * kNumXcd);
   const size_t part_elems = c.any_complex ? gram_partial_elems_c(ns, c.nd) : gram_partial_elems(ns, c.nd);
   if (assign) c.part_elems = part_elems;
   b.take(c.d_part, sizeof(double) * part_elems);
@@ -539,7 +537,7 @@ struct BProb {
 
 // One filter + Rayleigh-Ritz pass on every problem of a batch in lockstep:
 // per Chebyshev step the projections and scatters run per problem and the
-// stencils of all problems run as persistent launches (one per tile shape).
+// stencils of all problems run as one launch per tile shape.
 // The launches of the whole pass are planned first and their job tables
 // uploaded once, so the host never waits on the device inside the pass.
 // All contexts share the stream and the filter degree.
@@ -804,10 +802,7 @@ hcu_status batch_pass_t(std::vector<BProb>& probs, Ctx& lead, double* filter_ms)
     }
     for (size_t l = first[step]; l < first[step + 1]; ++l) {
       ProfScope ps(lead, PK_STENCIL);
-      // small launches (a few thousand items) run one workgroup per item: a
-      // persistent grid costs more to start and drain than it balances
-      const bool persistent = launches[l].total >= kPersistentMinItems;
-      hcu_status s = run_stencil_batch<T>(launches[l], lead.d_jobs, persistent ? lead.d_counters : nullptr, st);
+      hcu_status s = run_stencil_batch<T>(launches[l], lead.d_jobs, st);
       if (s != HCU_OK) return fail(lead, s, "batched stencil launch failed");
     }
     const bool batched_fused = fuse_all && step < m && fjob_n[step] > 0;
@@ -1151,13 +1146,11 @@ hcu_status autotune_t(Ctx& c, hcu_tuning* best) {
       if (TX > n1 || (ti > 0 && TX == txs[0])) continue;
       for (int TYt : {1, 2, 3, 4, 6, 8, 9, 12, 14, 16}) {
         if (TX * TYt > 1024 || TX * TYt < 64) continue;
-        for (int zd : {1, 2, 4}) {
+        for (int zd : {1, 2, 4, 8}) {
           const int tz = (n3 + zd - 1) / zd;
-          if (zd > 1 && tz < 8) continue;
-          for (int ring : {0, 1}) {
-            if (!stencil_shape_ok(c, TX, TYt, RY, tz, ring)) continue;
-            cands.push_back(hcu_tuning{TX, TYt, RY, tz, ring, 0.0});
-          }
+          if (zd > 1 && tz < 3) continue;
+          if (!stencil_shape_ok(c, TX, TYt, RY, tz, 0)) continue;
+          cands.push_back(hcu_tuning{TX, TYt, RY, tz, 0, 0.0});
         }
       }
     }
@@ -1760,7 +1753,7 @@ hcu_status hcu_scf_step(hcu_ctx* ctx, hcu_scf_step_info* info) {
       if (s != HCU_OK) return s;
     }
   } else {
-    // every (spin, k) block of the context in one persistent stencil launch per Chebyshev step
+    // every (spin, k) block of the context in one stencil launch per Chebyshev step
     std::vector<BProb> pr;
     for (int sp = 0; sp < c.p.nspin; ++sp)
       for (int k = 0; k < c.p.nk; ++k) pr.push_back(BProb{&c, sp, k, sk_index(c, sp, k), 0, 0, 0, 0});

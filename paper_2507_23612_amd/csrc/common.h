@@ -205,7 +205,6 @@ struct Ctx {
   std::vector<void*> d_Q;            // per (spin,k): coupled projections, transposed [nproj][ns]
   std::vector<void*> d_PY;           // per (spin,k): projections of the filtered block (for D)
   void* d_jobs = nullptr;            // batched-stencil job table (used when this context leads a batch)
-  unsigned long long* d_counters = nullptr;
   void* d_ppart = nullptr;           // projection partial sums [chunk][nproj][ns]
   std::vector<void*> d_ppart_sk;     // per (spin, k) block (several blocks in one fused launch); [0] = d_ppart
   // Hubbard forces and stress
@@ -397,7 +396,7 @@ template <typename T>
 void launch_stencil(const Ctx& c, int ik, const T* Yin, int64_t ld, const T* Yprev, int64_t ld_prev, T* Yout,
                     int64_t ld_out, int ncol, double alpha, double cshift, double beta, hipStream_t st);
 bool stencil_shape_ok(const Ctx& c, int TX, int TYt, int RY, int tz, int ring);
-// one block of a batched stencil step (stencil.hip, persistent launch)
+// one block of a batched stencil step (stencil.hip)
 struct StencilJob {
   const Ctx* c;
   int ik;
@@ -410,27 +409,23 @@ struct StencilJob {
   int ncol;
   double alpha, cshift, beta;
 };
-// Persistent stencil launches over many blocks, planned ahead: plan appends
-// the job records of one step (grouped by tile shape, one launch per group)
-// to `host` and the launches to `out`; after the caller has copied `host` to
-// the device job table, run issues one planned launch: persistent (fixed
-// grid draining per-XCD counters) when d_counters is given, else one
-// workgroup per work item.
+// Stencil launches over many blocks, planned ahead: plan appends the job
+// records of one step (grouped by tile shape, one launch per group) to `host`
+// and the launches to `out`; after the caller has copied `host` to the device
+// job table, run issues one planned launch, one workgroup per work item.
 struct BatchLaunch {
   size_t first;                 // first job record of the launch
   int njob;
   unsigned long long total;     // work items
   int TX, TYt, RY, R;
+  int vx;                       // points per vector
   int halo_slots;               // most halo values per thread and plane over the jobs
-  int ring;                     // halo ring (order-12 stencil only)
-  int halo_n;                   // most halo values per plane over the jobs
 };
 template <typename T>
 hcu_status plan_stencil_batch(const std::vector<StencilJob>& jobs, std::vector<unsigned char>& host,
                               std::vector<BatchLaunch>& out);
 template <typename T>
-hcu_status run_stencil_batch(const BatchLaunch& L, const void* d_jobs, unsigned long long* d_counters,
-                             hipStream_t st);
+hcu_status run_stencil_batch(const BatchLaunch& L, const void* d_jobs, hipStream_t st);
 // nonlocal.hip: Y += alpha * sum_j phi_j Qt[j][s]  (64-point bricks on the
 // matrix cores)
 template <typename T>

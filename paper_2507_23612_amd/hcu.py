@@ -510,7 +510,7 @@ class HcuContext:
 
 
 class HcuBatch:
-    """Several bound contexts advanced together (one persistent stencil
+    """Several bound contexts advanced together (one stencil
     launch per Chebyshev step over all their blocks).  Holds references to
     the contexts; does not own them."""
 

@@ -50,7 +50,7 @@ def _context(cfg, precision="fp64"):
 
 
 def _scf_group(ctxs, tol_d, tol_f, max_iter=100):
-    """Converge a group of contexts together (one persistent stencil launch
+    """Converge a group of contexts together (one stencil launch
     per Chebyshev step over all of them)."""
     from paper_2507_23612_amd import hcu
     b = hcu.HcuBatch(ctxs)
