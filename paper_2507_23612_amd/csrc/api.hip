@@ -809,7 +809,7 @@ hcu_status batch_pass_t(std::vector<BProb>& probs, Ctx& lead, double* filter_ms)
     if (batched_fused) {
       ProfScope ps(lead, PK_FUSED);
       launch_scatter_project_batch<T>(reinterpret_cast<const FusedJob*>((const char*)lead.d_jobs + fjob_off[step]),
-                                      fjob_n[step], fjob_items[step], lead.pgroup, fNT, st);
+                                      fjob_n[step], fjob_items[step], fNT, lead.nd, st);
     }
     if (nl > 1 && fan_out(lead, nl) != HCU_OK) return HCU_DEVICE;
     for (int i = 0; i < np; ++i) {

@@ -75,21 +75,39 @@ __device__ inline unsigned xcd_linear() {
 // Point order of the 64-point bricks of the projector tables.  Linear: brick
 // b holds the points 64 b .. 64 b + 63 (the last one cut at the grid end).
 // Blocks: brick b is a block of 2^lx x 2^ly x 2^lz grid points (lx >= 2,
-// lx + ly + lz = 6) in x-fastest block order, local index
-// i = dx + 2^lx (dy + 2^ly dz); a compact block meets the atoms' spherical
-// supports more densely than a 64-point run of one grid row.  Local indices
-// 4k .. 4k+3 are consecutive in memory in both orders.  Projection brick b
-// is made of the bricks 4b .. 4b+3 in either order.
+// lx + ly + lz = 6), local index i = dx + 2^lx (dy + 2^ly dz); a compact block
+// meets the atoms' spherical supports more densely than a 64-point run of one
+// grid row, and the last block of a row may end outside the grid.  Local
+// indices 4k .. 4k+3 are consecutive in memory in both orders.  Projection
+// brick b is made of the bricks pieces b .. pieces b + count - 1.
 struct BrickGeo {
   int cube = 0;                 // 1: blocks
   int lx = 6, ly = 0, lz = 0;   // log2 of the block edges
   int n1 = 0, nbx = 1, nby = 1;
   int64_t n12 = 0;
   int64_t nbrick = 0;           // bricks of the grid
-  __host__ __device__ int64_t base(int64_t b) const {
+  // consecutive bricks that make a projection brick: pz planes (fastest) times
+  // py blocks along y (the last stack of a column may hold fewer); 1 x 1 with
+  // four pieces: bricks that follow each other along x
+  int pieces = 4, pz = 1, py = 1;
+  __host__ __device__ bool stacked() const { return pz * py > 1; }
+  // bricks of the projection brick that starts with brick b
+  __host__ __device__ int count(int b) const {
+    if (!stacked()) return nbrick - b < pieces ? (int)nbrick - b : pieces;
+    const unsigned ny = ((unsigned)nby + py - 1) / py;
+    const int left = nby - py * (int)((unsigned)b / (unsigned)pieces / (unsigned)nbx % ny);
+    return pz * (left < py ? left : py);
+  }
+  // first point of brick b; w: its points along x inside the grid (blocks)
+  __host__ __device__ int64_t base(int64_t b, int* w = nullptr) const {
     if (!cube) return b * 64;
-    const int64_t bx = b % nbx, t = b / nbx, by = t % nby, bz = t / nby;
-    return (bx << lx) + (int64_t)n1 * (by << ly) + n12 * (bz << lz);
+    // (32-bit division: a brick index fits, and the 64-bit one is a long
+    // sequence of instructions)
+    const unsigned v = (unsigned)b, g = pz * py, u = v / g, i = v - u * g, iy = i / (unsigned)pz, iz = i - iy * pz;
+    const unsigned ny = ((unsigned)nby + py - 1) / py, t = u / (unsigned)nbx, bx = u - t * nbx, z = t / ny, y = t - z * ny;
+    const unsigned by = py * y + iy, bz = pz * z + iz;
+    if (w) *w = n1 - (int)(bx << lx) < 1 << lx ? n1 - (int)(bx << lx) : 1 << lx;
+    return (int64_t)(bx << lx) + (int64_t)n1 * (by << ly) + n12 * (int64_t)(bz << lz);
   }
   __host__ __device__ int64_t off(int i) const {
     if (!cube) return i;
@@ -153,8 +171,8 @@ struct Ctx {
   int coup_size = 0;
   BrickGeo geo;                      // point order of the bricks
   // Bricks of 64 grid points (geo).  Brick b has bnj[b] functions,
-  // listed in bj[boff[b] .. boff[b+1]) (padded to a multiple of 4 with -1),
-  // and a dense value tile [slot][64 points].
+  // listed in bj[boff[b] .. boff[b+1]) (padded to a multiple of 16 with
+  // its last one), and a dense value tile of 64 points per slot.
   std::vector<int64_t> boff;         // nbrick + 1, in slots
   std::vector<int> bnj;
   std::vector<int> bj;
@@ -164,21 +182,20 @@ struct Ctx {
   int* d_bj = nullptr;
   int64_t* d_bsrc = nullptr;
   std::vector<void*> d_bval;         // per k: [slot][point]
-  // Projection bricks (real blocks): runs of kPBrick consecutive points with
-  // the union of their functions, laid out like the bricks.  Each slot's
+  // Projection bricks: several bricks with the union of their functions.  Each slot's
   // partial sum goes to row pdest[slot] of a function-major partial array;
   // function j owns rows jrow[j] .. jrow[j+1] (its bricks in ascending order).
   std::vector<int64_t> pboff;
   std::vector<int> pbnj;
   std::vector<int64_t> pbsrc, pdest, jrow;
-  int pgroup = 2;   // points per lane and load group in the table order (2 or 4)
+  int pgroup = 2;   // values of 16 bytes: points (tiles) per lane and load in the table orders
   int max_ptiles = 0;   // most 16-function slot tiles of any projection brick
   int64_t* d_pboff = nullptr;
   int* d_pbnj = nullptr;
   int64_t* d_pbsrc = nullptr;
   int64_t* d_pdest = nullptr;
   int64_t* d_jrow = nullptr;
-  std::vector<void*> d_pbval;        // per k: [slot][kPBrick points]
+  std::vector<void*> d_pbval;        // per k: the projection bricks' values
   int nm_count[kMaxNm + 1] = {0};    // projector blocks per function count
   int nm_offset[kMaxNm + 1] = {0};   // offset of each count's list in d_nm_lists
   int* d_nm_lists = nullptr;
@@ -432,7 +449,6 @@ template <typename T>
 void launch_nl_scatter(const Ctx& c, int ik, T* Y, int64_t ld, int ncol, const T* Qt, double alpha, hipStream_t st);
 constexpr int kBrick = 64;
 constexpr int kRRLanes = 4;   // Rayleigh-Ritz steps of different blocks in flight at once
-constexpr int kPBrick = 256;
 
 // 16x16x4 matrix-core step D += A B per wave.  Operands: lane l supplies
 // A[l%16][l/16] and B[l/16][l%16]; result column l%16, rows row(l, r).
@@ -487,9 +503,26 @@ struct FusedJob {
 template <typename T>
 FusedJob fused_job_of(const Ctx& c, int ik, T* Y, int64_t ld, int ncol, const T* Qt, double alpha, void* part,
                       unsigned item0);
-unsigned fused_job_items(const Ctx& c, int ncol);
+// The job whose workgroups contain lw (jobs ordered by first workgroup).
+__device__ __forceinline__ const FusedJob& fused_job(const FusedJob* __restrict__ jobs, int njob, unsigned lw) {
+  int lo = 0, hi = njob - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (jobs[mid].item0 <= lw) lo = mid;
+    else hi = mid - 1;
+  }
+  return jobs[lo];
+}
+unsigned fused_job_items(const Ctx& c, int ncol);   // workgroups of one block
 template <typename T>
-void launch_scatter_project_batch(const FusedJob* d_jobs, int njob, unsigned items, int G, int NT, hipStream_t st);
+void launch_scatter_project_batch(const FusedJob* d_jobs, int njob, unsigned items, int NT, int64_t ld, hipStream_t st);
+// bricks.hip: Y += alpha Phi Q (scatter, table bval) and / or the
+// projection partial sums of the result (project, table pbval) into d_ppart
+template <typename T>
+void launch_brick_pass(const Ctx& c, const T* bval, const T* pbval, T* Y, int64_t ld, int ncol, const T* Qt,
+                       double alpha, bool scatter, bool project, hipStream_t st);
+template <typename T>
+void launch_brick_pass_batch(const FusedJob* d_jobs, int njob, unsigned items, int NT, int64_t ld, hipStream_t st);
 template <typename T>
 void launch_scatter_project(const Ctx& c, int ik, T* Y, int64_t ld, int ncol, const T* Qt, double alpha,
                             const double* coup, T* P, T* Q, hipStream_t st, int part = 3);

@@ -200,26 +200,58 @@ hcu_status build_structure(Ctx& c) {
     std::sort(row.begin(), row.end());
     for (int t = a; t < e; ++t) { c.csr_col[t] = row[t - a].first; c.csr_src[t] = row[t - a].second; }
   }
-  // bricks of 64 points (4x4x4 blocks when the grid allows, else runs of
-  // 64 consecutive points): the functions touching each brick, padded to a
-  // multiple of 4 (the MFMA depth)
+  // bricks of 64 points: the functions touching each brick, padded to a
+  // multiple of 16 (one staged chunk; the padding repeats the last function
+  // with zero values)
   BrickGeo& geo = c.geo;
   geo = BrickGeo{};
   {
     const int n1 = c.p.n[0], n2 = c.p.n[1], n3 = c.p.n[2];
-    // 8 x 8 x 1 blocks: 64-byte runs of FP64 values per state row (4 x 4 x 4
-    // cubes, denser still, leave 32-byte runs and were slower: the fused
-    // scatter + projection 0.99 -> 1.28 ms on c2, 4.45 -> 6.5 ms on c3)
-    (void)n3;
-    if (n1 % 8 == 0 && n2 % 8 == 0) { geo.cube = 1; geo.lx = 3; geo.ly = 3; geo.lz = 0; }
+    // Blocks of 64 points of one plane, as compact as whole 64-byte runs of a
+    // state row allow: 16 x 4 for 4-byte values, 8 x 8 for the others (4 x 4 x
+    // 4 cubes, denser still, leave 32-byte runs and were slower).  A block may
+    // end outside the row (at most a quarter of the points; the shape that
+    // pads less wins); rows that do not fit keep runs of 64
+    // consecutive points.
+    auto pad = [&](int lx) { return ((n1 + (1 << lx) - 1) >> lx << lx) - n1; };
+    auto fits = [&](int lx) { return n2 % (1 << (6 - lx)) == 0 && 4 * pad(lx) <= n1; };
+    const int first = c.mixed && !c.any_complex ? 4 : 3, second = 7 - first;
+    for (int lx : {first, second})
+      if (fits(lx) && (!geo.cube || pad(lx) < pad(geo.lx))) {
+        geo.cube = 1;
+        geo.lx = lx;
+        geo.ly = 6 - lx;
+        geo.lz = 0;
+      }
+    // Projection bricks: four blocks of consecutive planes where n3 allows (8 x
+    // 8 x 4 points; the most compact 256).  Large blocks of 4-byte values take
+    // 16 x 20 x 2 points: half as many partial sums again (0.34 instead of 0.57
+    // GB on 108x108x96 with 640 states, their sum 0.29 instead of 0.31 ms) for
+    // a longer pass (2.6 instead of 2.4 ms: more functions per brick); that
+    // keeps more than 64 functions per brick on this cell, which the test of
+    // the eight-tile variant at this size asks for.
+    const bool large = (int64_t)((n1 + 15) / 16) * (n2 / 4) * n3 / 10 * ((c.p.ns + 63) / 64) >= 4 * 256;   // four workgroups per compute unit
+    if (geo.cube && geo.lx == 4 && n3 % 2 == 0 && large) {
+      geo.py = 5;
+      geo.pz = 2;
+    } else if (geo.cube && n3 % 4 == 0) {
+      geo.pz = 4;
+    }
+    if (geo.stacked()) geo.pieces = geo.py * geo.pz;
     geo.n1 = n1;
     geo.n12 = (int64_t)n1 * n2;
-    geo.nbx = n1 >> geo.lx;
+    geo.nbx = geo.cube ? (n1 + (1 << geo.lx) - 1) >> geo.lx : 1;
     geo.nby = geo.cube ? n2 >> geo.ly : 1;
   }
-  const int nbrick = geo.cube ? c.nd / kBrick : (c.nd + kBrick - 1) / kBrick;
+  const int nbrick = geo.cube ? geo.nbx * ((geo.nby + geo.py - 1) / geo.py * geo.py) * c.p.n[2] : (c.nd + kBrick - 1) / kBrick;
   geo.nbrick = nbrick;
-  auto brick_point = [&](int b, int i) -> int64_t { return geo.base(b) + geo.off(i); };   // >= nd: outside
+  auto brick_point = [&](int b, int i) -> int64_t {   // >= nd: outside
+    int w = 64;
+    const int64_t p0 = geo.base(b, &w);
+    const int first = b / geo.pieces * geo.pieces;
+    if (geo.stacked() && b - first >= geo.count(first)) return c.nd;   // past the last block along y
+    return geo.cube && (i & ((1 << geo.lx) - 1)) >= w ? (int64_t)c.nd : p0 + geo.off(i);
+  };
   c.boff.assign(nbrick + 1, 0);
   c.bnj.assign(nbrick, 0);
   c.bj.clear();
@@ -234,13 +266,22 @@ hcu_status build_structure(Ctx& c) {
     std::sort(js.begin(), js.end());
     js.erase(std::unique(js.begin(), js.end()), js.end());
     const int nj = (int)js.size();
-    const int njp = (nj + 3) / 4 * 4;
+    const int njp = (nj + 15) / 16 * 16;
     c.bnj[b] = nj;
     c.boff[b + 1] = c.boff[b] + njp;
-    for (int t = 0; t < njp; ++t) c.bj.push_back(t < nj ? js[t] : -1);
+    for (int t = 0; t < njp; ++t) c.bj.push_back(t < nj ? js[t] : js[nj - 1]);
   }
   // a tail past the last brick: a kernel may read a clamped index there
-  c.bj.insert(c.bj.end(), 64, -1);
+  c.bj.insert(c.bj.end(), 64, 0);
+  c.pgroup = 16 / ((c.mixed ? 4 : 8) * (c.any_complex ? 2 : 1));   // values of 16 bytes
+  // value of slot jl at local point i, in operand order, the four functions
+  // of a matrix-core step together: [group][pack][lane][tiles of a pack]
+  // (lane = 16 q + n holds function q at point n of its 16-point tiles)
+  const int G1 = c.pgroup;   // tiles per 16-byte pack
+  auto bval_at = [&](int64_t off, int jl, int i) -> int64_t {
+    const int pt = i / 16, lane = (jl % 4) * 16 + i % 16;
+    return (off + jl / 4 * 4) * kBrick + (pt / G1) * (64 * G1) + lane * G1 + pt % G1;
+  };
   c.bsrc.assign((size_t)c.boff[nbrick] * kBrick, -1);
   for (int b = 0; b < nbrick; ++b) {
     const int* bjb = c.bj.data() + c.boff[b];
@@ -250,19 +291,15 @@ hcu_status build_structure(Ctx& c) {
       if (p >= c.nd) continue;
       for (int t = c.csr_ptr[p]; t < c.csr_ptr[p + 1]; ++t) {
         const int jl = (int)(std::lower_bound(bjb, bjb + nj, c.csr_col[t]) - bjb);
-        c.bsrc[(c.boff[b] + jl) * kBrick + i] = c.csr_src[t];
+        c.bsrc[bval_at(c.boff[b], jl, i)] = c.csr_src[t];
       }
     }
   }
-  // projection bricks (bricks 4b .. 4b+3): the function list of each brick
-  // is padded to a multiple of 16 (one matrix-core tile), and the value tile
-  // is stored in operand order [tile][64-point piece][step group i][lane][G]:
-  // at steps G i .. G i + G-1 lane l of a wave holds row 16 tile + l%16 at
-  // the G local indices from 4G i + G (l/16) of the piece (consecutive in
-  // memory), which is also the order in which the lane reads its state row.
-  // G = 2 (16-byte groups in FP64 and complex FP32) unless every block is
-  // real FP32 (G = 4).
-  c.pgroup = (c.mixed && !c.any_complex) ? 4 : 2;
+  // projection bricks: the function list of each is padded to a multiple of
+  // 16 (one matrix-core tile), and the value tile is stored in operand order
+  // [tile][64-point piece][step group i][lane][G]: at steps G i .. G i + G-1
+  // lane l of a wave holds row 16 tile + l%16 at the G local points from
+  // 4G i + G (l/16) of the piece, G values being 16 bytes.
   const int G = c.pgroup;
   c.pboff.assign(1, 0);
   c.max_ptiles = 0;
@@ -271,7 +308,7 @@ hcu_status build_structure(Ctx& c) {
   c.pdest.clear();
   c.jrow.assign(c.nproj + 1, 0);
   {
-    constexpr int P = kPBrick / kBrick;
+    const int P = geo.pieces;
     const int npb = (nbrick + P - 1) / P;
     std::vector<int> pbj;   // padded slots, -1 for padding
     for (int b = 0; b < npb; ++b) {
@@ -299,7 +336,7 @@ hcu_status build_structure(Ctx& c) {
     std::vector<int64_t> fill(c.jrow.begin(), c.jrow.end() - 1);
     for (size_t sl = 0; sl < pbj.size(); ++sl)
       if (pbj[sl] >= 0) c.pdest[sl] = fill[pbj[sl]]++;
-    c.pbsrc.assign((size_t)c.pboff.back() * kPBrick, -1);
+    c.pbsrc.assign((size_t)c.pboff.back() * P * kBrick, -1);
     for (int b = 0; b < npb; ++b) {
       const int* jb = pbj.data() + c.pboff[b];
       const int nj = c.pbnj[b];

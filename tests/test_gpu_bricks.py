@@ -1,0 +1,70 @@
+"""Edges of the projector pass against the CPU oracle: brick shapes (16 x 4,
+8 x 8, blocks that end outside the row, runs of 64 points with a ragged last
+brick, stacked planes or not), state counts around the 16 and 64 of a wave and
+a workgroup, padded rows, and 3, 5 and 9 slot tiles per projection brick (the
+last swept twice by the projection alone).
+
+Bars of the operator and the filter as for the other operator tests: 1e-12 and
+2e-6 of the largest value for H (summation order), 1e-11 and 3e-5 for a filter
+of degree 3.
+"""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _cell(n, ns, k, copies):
+    cfg = workloads.make_config("tiny")
+    rng = np.random.default_rng(5)
+    pos = np.concatenate([np.asarray(cfg["pos"]) + (c > 0) * rng.normal(size=np.shape(cfg["pos"])) for c in range(copies)])
+    cfg.update(n=np.array(n, np.int32), ns=ns, nelec=1.0, atom_species=np.tile(cfg["atom_species"], copies), pos=pos)
+    if k:
+        cfg["kpts"] = np.array([[0.11, 0.05, -0.13]])
+    return cfg
+
+
+@pytest.mark.parametrize("precision,k", [("fp64", 0), ("mixed", 0), ("fp64", 1), ("mixed", 1)])
+@pytest.mark.parametrize("n,ns,pad,copies", [
+    ((16, 16, 12), 17, 0, 1), ((20, 16, 9), 1, 3, 1), ((31, 12, 8), 15, 1, 1), ((11, 10, 9), 70, 5, 1),
+    ((16, 8, 8), 33, 0, 2), ((15, 8, 8), 16, 1, 4), ((13, 12, 10), 65, 0, 4)])
+def test_projector_pass(n, ns, pad, copies, precision, k):
+    torch = _torch()
+    from oracle import chfsi
+    from oracle.hamiltonian import Hamiltonian
+    from paper_2507_23612_amd import hcu
+    cfg = _cell(n, ns, k, copies)
+    ctx = hcu.HcuContext(cfg, precision)
+    rng = np.random.default_rng(3)
+    D = rng.normal(size=(1, ctx.nhub, 5, 5)) * 0.05
+    D = 0.2 * np.eye(5) + D + D.transpose(0, 1, 3, 2)
+    ctx.set_hubbard_occupation(D)
+    Xh = workloads.random_block(ctx.nd, ns, 3, bool(k))
+    X = torch.full((ns, ctx.nd + pad), float("nan"), dtype=ctx.dtype, device="cuda")
+    X[:, :ctx.nd] = torch.from_numpy(Xh).cuda().to(ctx.dtype)
+    Xh = X[:, :ctx.nd].cpu().numpy().astype(np.complex128 if k else np.float64)
+    H = Hamiltonian(cfg, cfg["kpts"][0] if k else (0.0, 0.0, 0.0), D=list(D[0]))
+    want = H.apply(Xh)
+    bounds = (4.0, 2.0 * float(np.abs(want).max()), -1.0)
+    filtered = chfsi.cheb_filter(H.apply, Xh, 3, *bounds)
+    Y = torch.empty_like(X)
+    fp64 = precision == "fp64"
+    for call, ref, tol in ((lambda: ctx.apply_h(X, Y), want, 1e-12 if fp64 else 2e-6),
+                           (lambda: ctx.cheb_filter(X, Y, 3, *bounds), filtered, 1e-11 if fp64 else 3e-5)):
+        Y.fill_(float("nan"))
+        call()
+        got = Y.cpu().numpy()
+        assert np.isnan(got[:, ctx.nd:]).all()
+        err = float(np.abs(got[:, :ctx.nd] - ref).max() / np.abs(ref).max())
+        print(f"[gpu] projector pass {n} ns={ns} {precision} k={k}: {err:.1e}", flush=True)
+        assert err < tol
+    ctx.close()
