@@ -855,35 +855,28 @@ hcu_status lanczos_t(Ctx& c, int spin, int ik, int steps, double* th_min, double
   T* v = (T*)c.d_vec;
   T* w = v + nd;
   T* vp = w + nd;
-  double* dres = c.d_scal + 8;
-  double hres[2];
-  auto dot = [&](const T* x, const T* y) -> double {
-    launch_dot<T>(c, x, y, nd, dres, c.stream);
-    hipMemcpyAsync(hres, dres, 2 * sizeof(double), hipMemcpyDeviceToHost, c.stream);
-    hipStreamSynchronize(c.stream);
-    return hres[0];
-  };
-  HCU_HIP(hipMemcpyAsync(v, c.d_v0[sk], esize(c) * nd, hipMemcpyDeviceToDevice, c.stream));
-  double nrm = std::sqrt(dot(v, v));
-  if (!(nrm > 0)) return fail(c, HCU_INVALID_ARG, "Lanczos start vector is zero");
-  launch_scale_copy<T>(v, v, 1.0 / nrm, nd, c.stream);
-  HCU_HIP(hipMemsetAsync(vp, 0, esize(c) * nd, c.stream));
+  // scalars of up to 24 steps at a time stay on the device: d_scal[8] = |v0|,
+  // [9] = the last beta, [16 ..] = alpha, [40 ..] = beta
+  constexpr int kBatch = 24;
+  double* const sc = c.d_scal;
+  launch_lanczos_start<T>(c, (const T*)c.d_v0[sk], v, vp, sc + 8, c.stream);
   std::vector<double> al, be;
-  double bprev = 0;
-  for (int j = 0; j < steps; ++j) {
-    apply_h_t<T>(c, spin, ik, v, nd, w, nd, 1);
-    const double alpha = dot(v, w);
-    launch_axpby<T>(c, w, v, -alpha, 0.0, 1.0, nd, c.stream);
-    if (j > 0) launch_axpby<T>(c, w, vp, -bprev, 0.0, 1.0, nd, c.stream);
-    const double beta = std::sqrt(dot(w, w));
-    al.push_back(alpha);
-    be.push_back(beta);
-    if (beta == 0.0) break;
-    HCU_HIP(hipMemcpyAsync(vp, v, esize(c) * nd, hipMemcpyDeviceToDevice, c.stream));
-    launch_scale_copy<T>(v, w, 1.0 / beta, nd, c.stream);
-    bprev = beta;
+  for (int j0 = 0; j0 < steps && (be.empty() || be.back() != 0.0); j0 += kBatch) {
+    const int m = std::min(kBatch, steps - j0);
+    for (int j = 0; j < m; ++j) {
+      apply_h_t<T>(c, spin, ik, v, nd, w, nd, 1);
+      launch_lanczos_step<T>(c, v, vp, w, j0 + j == 0, sc + 16 + j, sc + 40 + j, sc + 9, c.stream);
+    }
+    HCU_HIP(hipGetLastError());
+    double host[64];
+    HCU_HIP(hipMemcpyAsync(host + 8, sc + 8, 56 * sizeof(double), hipMemcpyDeviceToHost, c.stream));
+    HCU_HIP(hipStreamSynchronize(c.stream));
+    if (!(host[8] > 0)) return fail(c, HCU_INVALID_ARG, "Lanczos start vector is zero");
+    for (int j = 0; j < m && (be.empty() || be.back() != 0.0); ++j) {   // (a zero beta ends the recursion)
+      al.push_back(host[16 + j]);
+      be.push_back(host[40 + j]);
+    }
   }
-  HCU_HIP(hipStreamSynchronize(c.stream));
   const int n = (int)al.size();
   std::vector<double> Tm(n * n, 0.0), ev;
   for (int i = 0; i < n; ++i) {

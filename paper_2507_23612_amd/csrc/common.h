@@ -551,11 +551,10 @@ void launch_rotate_proj(const Ctx& c, const T* PY, const T* Cb, T* PX, int ncol,
 
 // scf_kernels.hip
 template <typename T>
-void launch_dot(const Ctx& c, const T* x, const T* y, int64_t n, double* out2, hipStream_t st);
+void launch_lanczos_start(const Ctx& c, const T* v0, T* v, T* vp, double* norm, hipStream_t st);
 template <typename T>
-void launch_axpby(const Ctx& c, T* y, const T* x, double a_re, double a_im, double b, int64_t n, hipStream_t st);
-template <typename T>
-void launch_scale_copy(T* dst, const T* src, double s, int64_t n, hipStream_t st);
+void launch_lanczos_step(const Ctx& c, T* v, T* vp, T* w, bool first, double* alpha, double* beta, double* carry,
+                         hipStream_t st);
 template <typename T>
 void launch_convert_c(const double* C, T* Cb, int n, int cplx, hipStream_t st);
 void launch_fermi(const Ctx& c, hipStream_t st);

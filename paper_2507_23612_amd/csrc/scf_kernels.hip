@@ -22,62 +22,101 @@ __device__ inline double block_sum(double v, double* sh) {
   return r;
 }
 
-// ------------------------------------------------------------------ dot
-// out2[0] = Re sum conj(x) y, out2[1] = Im; two deterministic stages.
+// ------------------------------------------------------------------ Lanczos
+// The vector part of a Lanczos recursion with its scalars on the device: the
+// 256 partial sums of a scalar product are summed by every workgroup that
+// needs the scalar (in the same order), so a step is three launches behind H
+// and nothing waits for the host.  (Scalars on the host, two round trips and
+// ten launches and copies per step: the 10-step bound of one 36x36x24 block
+// took 1.20 ms, 0.55 ms of it idle; this 0.49 ms.)
+constexpr int kLzParts = 256;
+
+// part[b] = workgroup b's share of Re sum conj(x) y
 template <typename T>
-__global__ void k_dot_part(const T* __restrict__ x, const T* __restrict__ y, int64_t n, double* part) {
+__global__ __launch_bounds__(256) void k_lz_dot(const T* __restrict__ x, const T* __restrict__ y, int64_t n,
+                                                double* __restrict__ part) {
   __shared__ double sh[256];
-  double re = 0, im = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    T p = mul_conj(y[i], x[i]);
+  double re = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
+    const T p = mul_conj(y[i], x[i]);
     if constexpr (sizeof(T) == sizeof(typename real_of<T>::type)) re += (double)p;
-    else { re += (double)p.re; im += (double)p.im; }
+    else re += (double)p.re;
   }
   re = block_sum(re, sh);
-  im = block_sum(im, sh);
-  if (threadIdx.x == 0) { part[2 * blockIdx.x] = re; part[2 * blockIdx.x + 1] = im; }
+  if (threadIdx.x == 0) part[blockIdx.x] = re;
 }
-__global__ void k_dot_final(const double* part, int np, double* out2) {
+
+// v = v0 / |v0|, vp = 0; *norm = |v0| from the partial sums of v0.v0
+template <typename T>
+__global__ __launch_bounds__(256) void k_lz_start(const T* __restrict__ v0, T* __restrict__ v, T* __restrict__ vp,
+                                                  int64_t n, const double* __restrict__ part, double* norm) {
   __shared__ double sh[256];
-  double re = 0, im = 0;
-  for (int i = threadIdx.x; i < np; i += blockDim.x) { re += part[2 * i]; im += part[2 * i + 1]; }
+  const double nrm = sqrt(block_sum(part[threadIdx.x], sh));
+  if (blockIdx.x == 0 && threadIdx.x == 0) *norm = nrm;
+  const auto f = (typename real_of<T>::type)(1.0 / nrm);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
+    v[i] = f * v0[i];
+    vp[i] = T(0);
+  }
+}
+
+// *alpha = the scalar product in part; w -= alpha v, then w -= *bprev vp
+// (bprev null: the first step); part2 = partial sums of w.w
+template <typename T>
+__global__ __launch_bounds__(256) void k_lz_orth(T* __restrict__ w, const T* __restrict__ v, const T* __restrict__ vp,
+                                                 int64_t n, const double* __restrict__ part, double* alpha,
+                                                 const double* bprev, double* __restrict__ part2) {
+  __shared__ double sh[256];
+  const double al = block_sum(part[threadIdx.x], sh);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = al;
+  const T a = make_scalar<T>(-al, 0.0), b = make_scalar<T>(bprev ? -*bprev : 0.0, 0.0);
+  double re = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
+    T x = w[i];
+    x += a * v[i];
+    if (bprev) x += b * vp[i];
+    w[i] = x;
+    const T p = mul_conj(x, x);
+    if constexpr (sizeof(T) == sizeof(typename real_of<T>::type)) re += (double)p;
+    else re += (double)p.re;
+  }
   re = block_sum(re, sh);
-  im = block_sum(im, sh);
-  if (threadIdx.x == 0) { out2[0] = re; out2[1] = im; }
+  if (threadIdx.x == 0) part2[blockIdx.x] = re;
+}
+
+// *beta = *carry = |w| from part2; vp = v, v = w / beta (beta = 0, the end of
+// the recursion: left alone)
+template <typename T>
+__global__ __launch_bounds__(256) void k_lz_next(T* __restrict__ v, T* __restrict__ vp, const T* __restrict__ w,
+                                                 int64_t n, const double* __restrict__ part2, double* beta,
+                                                 double* carry) {
+  __shared__ double sh[256];
+  const double be = sqrt(block_sum(part2[threadIdx.x], sh));
+  if (blockIdx.x == 0 && threadIdx.x == 0) *beta = *carry = be;
+  if (be == 0.0) return;
+  const auto f = (typename real_of<T>::type)(1.0 / be);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
+    vp[i] = v[i];
+    v[i] = f * w[i];
+  }
 }
 
 template <typename T>
-void launch_dot(const Ctx& c, const T* x, const T* y, int64_t n, double* out2, hipStream_t st) {
-  const int np = 256;
-  k_dot_part<T><<<np, 256, 0, st>>>(x, y, n, c.d_red);
-  k_dot_final<<<1, 256, 0, st>>>(c.d_red, np, out2);
+void launch_lanczos_start(const Ctx& c, const T* v0, T* v, T* vp, double* norm, hipStream_t st) {
+  launch_k(k_lz_dot<T>, kLzParts, 256, 0, st, v0, v0, (int64_t)c.nd, c.d_red);
+  launch_k(k_lz_start<T>, kLzParts, 256, 0, st, v0, v, vp, (int64_t)c.nd, (const double*)c.d_red, norm);
 }
 
-// y = a x + b y (a complex, b real)
+// the step behind w = H v; carry: the last step's beta in, this one's out
 template <typename T>
-__global__ void k_axpby(T* y, const T* x, double are, double aim, double b, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  using R = typename real_of<T>::type;
-  T a = make_scalar<T>(are, aim);
-  T v = (R)b * y[i];
-  if (x) v += a * x[i];
-  y[i] = v;
-}
-template <typename T>
-void launch_axpby(const Ctx& c, T* y, const T* x, double a_re, double a_im, double b, int64_t n, hipStream_t st) {
-  (void)c;
-  k_axpby<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(y, x, a_re, a_im, b, n);
-}
-
-template <typename T>
-__global__ void k_scale_copy(T* dst, const T* src, double s, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = (typename real_of<T>::type)s * src[i];
-}
-template <typename T>
-void launch_scale_copy(T* dst, const T* src, double s, int64_t n, hipStream_t st) {
-  k_scale_copy<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(dst, src, s, n);
+void launch_lanczos_step(const Ctx& c, T* v, T* vp, T* w, bool first, double* alpha, double* beta, double* carry,
+                         hipStream_t st) {
+  const int64_t n = c.nd;
+  double* const part2 = c.d_red + kLzParts;
+  launch_k(k_lz_dot<T>, kLzParts, 256, 0, st, (const T*)v, (const T*)w, n, c.d_red);
+  launch_k(k_lz_orth<T>, kLzParts, 256, 0, st, w, (const T*)v, (const T*)vp, n, (const double*)c.d_red, alpha,
+           first ? (const double*)nullptr : (const double*)carry, part2);
+  launch_k(k_lz_next<T>, kLzParts, 256, 0, st, v, vp, (const T*)w, n, (const double*)part2, beta, carry);
 }
 
 // eigenvectors (double, or interleaved double complex) -> block precision
@@ -246,9 +285,8 @@ void launch_density(const Ctx& c, const T* X, int64_t ld, const double* occ, dou
 }
 
 #define INST(T)                                                                                        \
-  template void launch_dot<T>(const Ctx&, const T*, const T*, int64_t, double*, hipStream_t);         \
-  template void launch_axpby<T>(const Ctx&, T*, const T*, double, double, double, int64_t, hipStream_t); \
-  template void launch_scale_copy<T>(T*, const T*, double, int64_t, hipStream_t);                      \
+  template void launch_lanczos_start<T>(const Ctx&, const T*, T*, T*, double*, hipStream_t);          \
+  template void launch_lanczos_step<T>(const Ctx&, T*, T*, T*, bool, double*, double*, double*, hipStream_t); \
   template void launch_convert_c<T>(const double*, T*, int, int, hipStream_t);                         \
   template void launch_occupation_matrix<T>(const Ctx&, int, int, const T*, hipStream_t);              \
   template void launch_density<T>(const Ctx&, const T*, int64_t, const double*, double, double*, hipStream_t);
