@@ -226,6 +226,11 @@ void small_sym_eigvals(std::vector<double> A, int n, std::vector<double>& ev) {
 // and d_Hs with C.  Sets d_info (nonzero: S not positive definite or the
 // tridiagonal eigensolver did not converge).
 hcu_status generalized_eig(Ctx& c, int n, bool cp, double* lam) {
+  if (geig_small_ok(n)) {
+    if (cp) launch_geig_small<cplx<double>>((cplx<double>*)c.d_S, (cplx<double>*)c.d_Hs, n, lam, c.d_info, c.stream);
+    else launch_geig_small<double>(c.d_S, c.d_Hs, n, lam, c.d_info, c.stream);
+    return HCU_OK;
+  }
   rocblas_status r;
   launch_rr_guard_in(c.d_S, c.d_Hs, n, cp ? 2 : 1, c.d_info, c.stream);
   if (cp) {

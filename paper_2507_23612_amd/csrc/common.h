@@ -393,6 +393,11 @@ hcu_status device_tables(Ctx& c);            // device: V_loc, csc/csr values, L
 void fill_stencil_coef(const Ctx& c, int ik, StencilCoef& sc);
 
 // eig.hip: Householder tridiagonalization of the Rayleigh-Ritz matrix in one workgroup
+// Hs C = S C diag(lam) of a small block (n x n column-major, upper triangles):
+// S becomes its Cholesky factor, Hs C; info[0 .. 2] as in generalized_eig
+bool geig_small_ok(int n);
+template <typename T>
+void launch_geig_small(T* S, T* Hs, int n, double* lam, int* info, hipStream_t st);
 bool sytrd_small_ok(int n);
 void launch_sytrd_small(double* A, int n, int lda, double* d, double* e, double* tau, hipStream_t st);
 bool hetrd_small_ok(int n);

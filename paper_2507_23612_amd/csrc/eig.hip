@@ -524,7 +524,268 @@ __global__ __launch_bounds__(kTdThreads) void k_hetrd_small(zc* __restrict__ A, 
   }
 }
 
+// ---------------------------------------------------------------- n <= 64
+// The whole generalized eigensolve Hs C = S C diag(lam) of a small block in
+// one workgroup, in LDS: Cholesky factor S = U^H U, A = U^-H Hs U^-1, cyclic
+// Jacobi rotations of A (n / 2 disjoint pairs at a time, every 2 x 2 block of
+// pairs updated by one thread), C = U^-1 Q.  One complex block of 32 states:
+// 0.18 ms; the library's chain took 1.1 ms in about 150 launches, more than
+// the host can issue when a pass has many small blocks (two spins and 8
+// k-points of the 6-atom cell: the SCF 82 -> 67 ms).  From 65 states on the
+// two matrices no longer fit the LDS and the rotations' 10 n^3 work in one
+// workgroup nears the chain's time.
+//
+// Pair (p, q), A_pq = r e^{i phi}: with theta = (A_qq - A_pp) / 2r,
+// t = sign(theta) / (|theta| + sqrt(theta^2 + 1)), c = 1 / sqrt(t^2 + 1),
+// s = t c, the columns become c a_p - s e^{-i phi} a_q and
+// s a_p + c e^{-i phi} a_q (rows conjugated) and A_pp, A_qq change by -+ t r.
+// Sweeps end when the off-diagonal elements met in one were below 1e-14 of
+// the matrix (they converge quadratically, so what is left is far smaller).
+constexpr int kJacMaxN = 64;
+constexpr int kJacSweeps = 40;
+
+template <typename T, int N>
+struct JacLds {
+  static constexpr int L = N + 1;   // padded column
+  alignas(16) unsigned char a[sizeof(T) * N * L], v[sizeof(T) * N * L];   // A (later U), and U (later Q)
+  alignas(16) unsigned char e[sizeof(T) * N / 2];
+  double c[N / 2], s[N / 2], tr[N / 2], inv[N], lam[N], red[N / 2];
+  int p[N / 2], q[N / 2], rank[N];
+  int stop;
+};
+
+template <typename T, int N>
+__global__ __launch_bounds__(N * 16) void k_geig_small(T* __restrict__ S, T* __restrict__ Hs, int n,
+                                                       double* __restrict__ lam, int* __restrict__ info) {
+  constexpr int L = JacLds<T, N>::L, BD = N * 16, kItems = 3;
+  __shared__ JacLds<T, N> sh;
+  T* const A = reinterpret_cast<T*>(sh.a);
+  T* const V = reinterpret_cast<T*>(sh.v);
+  T* const E = reinterpret_cast<T*>(sh.e);
+  const int t = threadIdx.x;
+  auto re = [](const T& x) -> double {
+    if constexpr (sizeof(T) == 8) return x;
+    else return x.re;
+  };
+  // both matrices from their upper triangles; non-finite entries: identities
+  int bad = 0;
+  for (int e = t; e < N * L; e += BD) A[e] = V[e] = T(0);
+  __syncthreads();
+  for (int e = t; e < n * n; e += BD) {
+    const int i = e % n, j = e / n;
+    if (i > j) continue;
+    const T h = Hs[e], u = S[e];
+    if (!isfinite(abs2_(h)) || !isfinite(abs2_(u))) {
+      if constexpr (sizeof(T) == 8) bad |= !isfinite(h) || !isfinite(u);
+      else bad |= !isfinite(h.re) || !isfinite(h.im) || !isfinite(u.re) || !isfinite(u.im);
+    }
+    A[j * L + i] = i == j ? T(re(h)) : h;
+    A[i * L + j] = i == j ? T(re(h)) : conj_(h);
+    V[j * L + i] = u;
+  }
+  bad = __syncthreads_or(bad);
+  auto identities = [&]() {
+    for (int e = t; e < N * L; e += BD) {
+      const T x(e / L == e % L && e / L < n ? 1.0 : 0.0);
+      A[e] = x;
+      V[e] = x;
+    }
+    __syncthreads();
+  };
+  if (bad) identities();
+  // S = U^H U in V, rows unscaled until the end
+  int chol = 0;
+  for (int k = 0; k < n && !chol; ++k) {
+    const double d = re(V[k * L + k]);
+    if (!(d > 0)) { chol = k + 1; break; }   // (uniform)
+    const double di = 1.0 / d;
+    const int m = n - 1 - k;
+    for (int e = t; e < m * m; e += BD) {
+      const int i = k + 1 + e % m, j = k + 1 + e / m;
+      if (i <= j) V[j * L + i] += T(-1.0) * (conj_(V[i * L + k]) * (di * V[j * L + k]));
+    }
+    __syncthreads();
+  }
+  if (chol) {
+    __syncthreads();
+    identities();
+  }
+  if (t < n) sh.inv[t] = 1.0 / sqrt(re(V[t * L + t]));
+  __syncthreads();
+  for (int e = t; e < n * n; e += BD) {
+    const int i = e % n, j = e / n;
+    if (i <= j) V[j * L + i] = sh.inv[i] * V[j * L + i];
+  }
+  __syncthreads();
+  // (inv[i] is 1 / U_ii from here on: U_ii = d / sqrt(d))
+  for (int e = t; e < n * n; e += BD) {   // U to memory: the area becomes Q
+    const int i = e % n, j = e / n;
+    S[e] = i <= j ? V[j * L + i] : T(0);
+  }
+  // A = U^-H A U^-1, the rows (columns) unscaled until the end of each solve
+  for (int k = 0; k < n; ++k) {
+    const double f = -sh.inv[k];
+    const int m = n - 1 - k;
+    for (int e = t; e < m * n; e += BD) {
+      const int i = k + 1 + e % m, j = e / m;
+      A[j * L + i] += conj_(V[i * L + k]) * (f * A[j * L + k]);
+    }
+    __syncthreads();
+  }
+  for (int e = t; e < n * n; e += BD) {
+    const int i = e % n, j = e / n;
+    A[j * L + i] = sh.inv[i] * A[j * L + i];
+  }
+  __syncthreads();
+  for (int k = 0; k < n; ++k) {
+    const double f = -sh.inv[k];
+    const int m = n - 1 - k;
+    for (int e = t; e < m * n; e += BD) {
+      const int i = e % n, j = k + 1 + e / n;
+      A[j * L + i] += (f * A[k * L + i]) * V[j * L + k];
+    }
+    __syncthreads();
+  }
+  for (int e = t; e < n * n; e += BD) {   // Hermitian from the upper triangle, real diagonal
+    const int i = e % n, j = e / n;
+    if (i > j) continue;
+    const T x = sh.inv[j] * A[j * L + i];
+    A[j * L + i] = i == j ? T(re(x)) : x;
+    A[i * L + j] = i == j ? T(re(x)) : conj_(x);
+  }
+  __syncthreads();
+  for (int e = t; e < N * L; e += BD) V[e] = T(e / L == e % L ? 1.0 : 0.0);
+  if (t < N / 2) {   // |A|^2, rows t and t + N / 2
+    double x = 0;
+    for (int j = 0; j < n; ++j) {
+      if (t < n) x += abs2_(A[j * L + t]);
+      if (t + N / 2 < n) x += abs2_(A[j * L + t + N / 2]);
+    }
+    sh.red[t] = x;
+  }
+  __syncthreads();
+  double norm2 = 0;
+  for (int i = 0; i < N / 2; ++i) norm2 += sh.red[i];
+  // rotations; an odd n gets a zero row and column, never rotated
+  const int M = (n + 1) & ~1, m = M / 2;
+  int ia[kItems], ib[kItems];   // the thread's shares of a round: (pair, pair) of A, then (row, pair) of V
+  for (int x = 0; x < kItems; ++x) {
+    const int it = t + x * BD, w = it - m * m;
+    ia[x] = it < m * m ? it % m : w < M * m ? M + w % M : -1;
+    ib[x] = it < m * m ? it / m : w / M;
+  }
+  int sweep = 0;
+  for (; sweep < kJacSweeps; ++sweep) {
+    double off = 0;
+    for (int r = 0; r < M - 1; ++r) {
+      if (t < m) {
+        const int p = t == 0 ? M - 1 : (r + t) % (M - 1), q = t == 0 ? r : (r - t + M - 1) % (M - 1);
+        double c = 1, s = 0, tr = 0;
+        T ph(1.0);
+        if (p < n && q < n) {
+          const T x = A[q * L + p];
+          const double r2 = abs2_(x), rr = sqrt(r2);
+          off += r2;
+          if (rr > 0) {
+            const double th = (re(A[q * L + q]) - re(A[p * L + p])) / (2 * rr);
+            const double tn = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1));
+            c = 1 / sqrt(tn * tn + 1);
+            s = tn * c;
+            tr = tn * rr;
+            ph = (1 / rr) * conj_(x);   // e^{-i phi}
+          }
+        }
+        sh.p[t] = p;
+        sh.q[t] = q;
+        sh.c[t] = c;
+        sh.s[t] = s;
+        sh.tr[t] = tr;
+        E[t] = ph;
+      }
+      __syncthreads();
+      for (int x = 0; x < kItems; ++x) {
+        if (ia[x] < 0) continue;
+        const int kq = ib[x], q1 = sh.p[kq] * L, q2 = sh.q[kq] * L;
+        const double c = sh.c[kq], s = sh.s[kq];
+        const T e = E[kq];
+        if (ia[x] >= M) {   // a row of Q
+          const int i = ia[x] - M;
+          const T v1 = V[q1 + i], v2 = e * V[q2 + i];
+          V[q1 + i] = c * v1 - s * v2;
+          V[q2 + i] = s * v1 + c * v2;
+          continue;
+        }
+        const int kp = ia[x], p1 = sh.p[kp], p2 = sh.q[kp];
+        if (kp == kq) {
+          const double tr = sh.tr[kp];
+          if (tr != 0) {
+            A[q1 + p1] = T(re(A[q1 + p1]) - tr);
+            A[q2 + p2] = T(re(A[q2 + p2]) + tr);
+          }
+          if (s != 0) A[q1 + p2] = A[q2 + p1] = T(0);
+          continue;
+        }
+        const T a11 = A[q1 + p1], a12 = e * A[q2 + p1], a21 = A[q1 + p2], a22 = e * A[q2 + p2];
+        const double cp = sh.c[kp], sp = sh.s[kp];
+        const T ep = conj_(E[kp]);
+        const T t11 = c * a11 - s * a12, t12 = s * a11 + c * a12;
+        const T t21 = ep * (c * a21 - s * a22), t22 = ep * (s * a21 + c * a22);
+        A[q1 + p1] = cp * t11 - sp * t21;
+        A[q2 + p1] = cp * t12 - sp * t22;
+        A[q1 + p2] = sp * t11 + cp * t21;
+        A[q2 + p2] = sp * t12 + cp * t22;
+      }
+      __syncthreads();
+    }
+    if (t < N / 2) sh.red[t] = t < m ? off : 0.0;
+    __syncthreads();
+    double off2 = 0;
+    for (int i = 0; i < N / 2; ++i) off2 += sh.red[i];
+    __syncthreads();
+    if (2 * off2 <= 1e-28 * norm2) break;   // (uniform)
+  }
+  // ascending order, C = U^-1 Q
+  if (t < n) sh.lam[t] = re(A[t * L + t]);
+  __syncthreads();
+  if (t < n) {
+    const double x = sh.lam[t];
+    int k = 0;
+    for (int j = 0; j < n; ++j) k += sh.lam[j] < x || (sh.lam[j] == x && j < t) ? 1 : 0;
+    sh.rank[t] = k;
+    lam[k] = x;
+  }
+  for (int e = t; e < n * n; e += BD) A[(e / n) * L + e % n] = S[e];   // U (each element by the thread that wrote it)
+  __syncthreads();
+  for (int k = n - 1; k >= 0; --k) {
+    const double f = -sh.inv[k];
+    for (int e = t; e < k * n; e += BD) {
+      const int i = e % k, j = e / k;
+      V[j * L + i] += A[k * L + i] * (f * V[j * L + k]);
+    }
+    __syncthreads();
+  }
+  for (int e = t; e < n * n; e += BD) {
+    const int i = e % n, j = e / n;
+    Hs[(int64_t)sh.rank[j] * n + i] = sh.inv[i] * V[j * L + i];
+  }
+  if (t == 0) {
+    info[0] = chol;
+    info[1] = sweep < kJacSweeps ? 0 : 1;
+    info[2] = bad;
+  }
+}
+
 }  // namespace
+
+bool geig_small_ok(int n) { return n >= 1 && n <= kJacMaxN; }
+
+template <typename T>
+void launch_geig_small(T* S, T* Hs, int n, double* lam, int* info, hipStream_t st) {
+  if (n <= 32) launch_k(k_geig_small<T, 32>, 1, 32 * 16, 0, st, S, Hs, n, lam, info);
+  else launch_k(k_geig_small<T, 64>, 1, 64 * 16, 0, st, S, Hs, n, lam, info);
+}
+template void launch_geig_small<double>(double*, double*, int, double*, int*, hipStream_t);
+template void launch_geig_small<cplx<double>>(cplx<double>*, cplx<double>*, int, double*, int*, hipStream_t);
 
 bool hetrd_small_ok(int n) { return n >= 1 && n <= kTdMaxN; }
 
