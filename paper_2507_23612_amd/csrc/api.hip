@@ -36,7 +36,7 @@ struct Bump {
 size_t esize(const Ctx& c) { return (c.mixed ? 4 : 8) * (c.any_complex ? 2 : 1); }
 
 constexpr int kInfoPerBlock = 4;   // eigensolve status words per (spin, k): Cholesky, eigensolver, guard
-constexpr size_t kBatchJobBytes = 1 << 20;   // stencil job records of one batched pass (~2900 jobs)
+constexpr size_t kBatchJobBytes = (1 << 20) + (1 << 18);   // job records of one batched pass (~2900 jobs)
 
 // Workspace layout.  Buffers whose size does not depend on the atom
 // positions come first (orbitals, work blocks, small dense buffers), then the
@@ -363,21 +363,6 @@ void scatter_project_t(Ctx& c, int spin, int ik, T* Y, int64_t ldy, int ncol, do
   ProfScope ps(c, PK_SCATTER);   // partial sums and coupling of the projections
   launch_scatter_project<T>(c, ik, Y, ldy, ncol, (const T*)c.d_Q[sk], alpha, c.d_coup[spin], (T*)c.d_P[sk],
                             (T*)c.d_Q[sk], c.stream, 2);
-}
-
-// The partial sums and coupling that follow a fused pass run in a batched
-// launch, reading block sk's own partials.
-template <typename T>
-void scatter_project_tail_t(Ctx& c, int spin, int ik, T* Y, int64_t ldy, int ncol, double alpha) {
-  const int sk = sk_index(c, spin, ik);
-  void* const p0 = c.d_ppart;
-  c.d_ppart = c.d_ppart_sk[sk];
-  {
-    ProfScope ps(c, PK_SCATTER);
-    launch_scatter_project<T>(c, ik, Y, ldy, ncol, (const T*)c.d_Q[sk], alpha, c.d_coup[spin], (T*)c.d_P[sk],
-                              (T*)c.d_Q[sk], c.stream, 2);
-  }
-  c.d_ppart = p0;
 }
 
 // proj_in = false: P and Q of X are already current (left by the step that
@@ -728,7 +713,16 @@ hcu_status batch_pass_t(std::vector<BProb>& probs, Ctx& lead, double* filter_ms)
   std::vector<int> fjob_n(m, 0);
   std::vector<unsigned> fjob_items(m, 0);
   int fNT = 4;
+  size_t tail_off = 0;   // the blocks' sums and couplings, the same in every step
   if (fuse_all) {
+    host.resize((host.size() + 15) & ~size_t(15), 0);
+    tail_off = host.size();
+    host.resize(tail_off + np * sizeof(TailJob));
+    for (int i = 0; i < np; ++i) {
+      const BProb& q = probs[i];
+      const TailJob t{q.c->d_ppart_sk[q.sk], q.c->d_P[q.sk], q.c->d_Q[q.sk], q.c->d_coup[q.spin]};
+      std::memcpy(host.data() + tail_off + i * sizeof(TailJob), &t, sizeof(t));
+    }
     for (int step = 0; step < m; ++step) {
       host.resize((host.size() + 15) & ~size_t(15), 0);
       fjob_off[step] = host.size();
@@ -812,21 +806,23 @@ hcu_status batch_pass_t(std::vector<BProb>& probs, Ctx& lead, double* filter_ms)
     }
     const bool batched_fused = fuse_all && step < m && fjob_n[step] > 0;
     if (batched_fused) {
-      ProfScope ps(lead, PK_FUSED);
-      launch_scatter_project_batch<T>(reinterpret_cast<const FusedJob*>((const char*)lead.d_jobs + fjob_off[step]),
-                                      fjob_n[step], fjob_items[step], fNT, lead.nd, st);
+      {
+        ProfScope ps(lead, PK_FUSED);
+        launch_scatter_project_batch<T>(reinterpret_cast<const FusedJob*>((const char*)lead.d_jobs + fjob_off[step]),
+                                        fjob_n[step], fjob_items[step], fNT, lead.nd, st);
+      }
+      ProfScope pt(lead, PK_SCATTER);   // (every block is one context's)
+      launch_sum_couple<T>(*probs[0].c, reinterpret_cast<const TailJob*>((const char*)lead.d_jobs + tail_off), np,
+                           TailJob{}, lead.p.ns, st);
     }
     if (nl > 1 && fan_out(lead, nl) != HCU_OK) return HCU_DEVICE;
     for (int i = 0; i < np; ++i) {
       BProb& q = probs[i];
-      if (q.c->nproj > 0) {
+      if (q.c->nproj > 0 && !batched_fused) {
         StreamSwap sw(*q.c, lane_stream(i));
         // steps before the last leave the projections of their output (the
         // next step's input) behind
-        if (batched_fused)
-          scatter_project_tail_t<T>(*q.c, q.spin, q.ik, (T*)ops[step][i].out, q.c->nd, q.c->p.ns,
-                                    ops[step][i].alpha);
-        else if (step < m && scatter_project_ok<T>(*q.c))
+        if (step < m && scatter_project_ok<T>(*q.c))
           scatter_project_t<T>(*q.c, q.spin, q.ik, (T*)ops[step][i].out, q.c->nd, q.c->p.ns, ops[step][i].alpha);
         else
           scatter_t<T>(*q.c, q.spin, q.ik, (T*)ops[step][i].out, q.c->nd, q.c->p.ns, ops[step][i].alpha);

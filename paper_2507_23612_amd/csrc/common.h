@@ -496,6 +496,16 @@ template <typename T>
 bool scatter_project_ok(const Ctx& c);
 // The fused pass of several blocks in one launch: one record per block,
 // workgroups item0 .. of each job (jobs ordered by item0).
+// The sums and the coupling behind a fused pass of one block: P and Q from the
+// partials (njob jobs of a device table, or one given by value).
+struct TailJob {
+  const void* part;
+  void* P;
+  void* Q;
+  const double* coup;
+};
+template <typename T>
+void launch_sum_couple(const Ctx& c, const TailJob* d_jobs, int njob, const TailJob& one, int ncol, hipStream_t st);
 struct FusedJob {
   BrickGeo geo;
   void* Y; int64_t ld; int ncol; int nst;

@@ -20,15 +20,21 @@
 namespace hcu {
 
 // Stage 2: P[s][j] = dV * sum of rows jrow[j] .. jrow[j+1] of part (fixed
-// order).  One workgroup per (j, 64 states); its 16 waves take every 16th
-// row and are combined in a fixed order.
-template <typename T>
-__global__ __launch_bounds__(1024) void k_slot_sum(const T* __restrict__ part, int ldp, int ncol,
-                                                   const int64_t* __restrict__ jrow, T* __restrict__ P, int nproj,
-                                                   double dv) {
+// order).  One workgroup per (j, 64 states, job); its 16 waves take every 16th
+// row and are combined in a fixed order.  JOBS: the pointers of job z instead
+// of those given.  Bound by reading the partials: 41 us for the 126 MB of
+// 72x72x96, 256 states (four rows under way per wave instead of two: 42 us).
+template <typename T, bool JOBS>
+__global__ __launch_bounds__(1024) void k_slot_sum(const TailJob* __restrict__ jobs, const T* __restrict__ part,
+                                                   T* __restrict__ P, int ldp, int ncol,
+                                                   const int64_t* __restrict__ jrow, int nproj, double dv) {
   using RT = typename real_of<T>::type;
   __shared__ __attribute__((aligned(16))) unsigned char red_raw[16 * 64 * sizeof(T)];
   T(*red)[64] = reinterpret_cast<T(*)[64]>(red_raw);
+  if constexpr (JOBS) {
+    part = (const T*)jobs[blockIdx.z].part;
+    P = (T*)jobs[blockIdx.z].P;
+  }
   const int j = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int s = blockIdx.x * 64 + lane;
@@ -51,23 +57,66 @@ __global__ __launch_bounds__(1024) void k_slot_sum(const T* __restrict__ part, i
   }
 }
 
-// Q[j0+m][s] = sum_m' C_b[m][m'] P[s][j0+m'], one thread per (block, state).
-template <typename T>
-__global__ void k_couple(const T* __restrict__ P, const BlockDesc* __restrict__ blocks, int ncol,
-                         const double* __restrict__ coup, T* __restrict__ Q, int nproj, int ldq) {
+// Q[j0+m][s] = sum_m' C_b[m][m'] P[s][j0+m'], one thread per (block, state, job).
+template <typename T, bool JOBS>
+__global__ __launch_bounds__(64) void k_couple(const TailJob* __restrict__ jobs, const T* __restrict__ P, const double* __restrict__ coup,
+                         T* __restrict__ Q, const BlockDesc* __restrict__ blocks, int ncol, int nproj, int ldq) {
+  if constexpr (JOBS) {
+    P = (const T*)jobs[blockIdx.z].P;
+    Q = (T*)jobs[blockIdx.z].Q;
+    coup = jobs[blockIdx.z].coup;
+  }
   const BlockDesc& b = blocks[blockIdx.y];
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= ncol) return;
   using RT = typename real_of<T>::type;
+  // (full loops over kMaxNm with guards: the values stay in registers, and
+  // their loads go out together from clamped addresses)
+  const int nm = b.nm;
+  const double* __restrict__ cb = coup + b.coup_off;
   T pv[kMaxNm];
-  for (int m = 0; m < b.nm; ++m) pv[m] = P[(int64_t)s * nproj + b.j0 + m];
-  const double* cb = coup + b.coup_off;
-  for (int m = 0; m < b.nm; ++m) {
+  for (int m = 0; m < kMaxNm; ++m) pv[m] = P[(int64_t)s * nproj + b.j0 + min(m, nm - 1)];
+  for (int m = 0; m < nm; ++m) {
     T qv = T(0);
-    for (int mp = 0; mp < b.nm; ++mp) qv += (RT)cb[m * b.nm + mp] * pv[mp];
+    for (int mp = 0; mp < kMaxNm; ++mp) {
+      const RT f = (RT)cb[m * nm + min(mp, nm - 1)];
+      if (mp < nm) qv += f * pv[mp];
+    }
     Q[(int64_t)(b.j0 + m) * ldq + s] = qv;
   }
 }
+
+// Several blocks of one context in one launch each: 16 complex FP32 blocks of
+// 36x36x24, 32 states, block by block took 155 us per step (the SCF of two spins
+// and 8 k-points 67 ms; 55 ms this way).
+template <typename T>
+static void launch_slot_sum(const Ctx& c, const TailJob* d_jobs, int njob, const TailJob& one, int ncol, hipStream_t st) {
+  auto run = [&](auto k) {
+    launch_k(k, dim3((ncol + 63) / 64, c.nproj, njob), 1024, 0, st, d_jobs, (const T*)one.part, (T*)one.P, c.p.ns, ncol,
+             c.d_jrow, c.nproj, c.dv);
+  };
+  if (d_jobs) run(k_slot_sum<T, true>);
+  else run(k_slot_sum<T, false>);
+}
+template <typename T>
+static void launch_couple_jobs(const Ctx& c, const TailJob* d_jobs, int njob, const TailJob& one, int ncol,
+                               hipStream_t st) {
+  auto run = [&](auto k) {
+    launch_k(k, dim3((ncol + 63) / 64, (unsigned)c.blocks.size(), njob), 64, 0, st, d_jobs, (const T*)one.P, one.coup,
+             (T*)one.Q, c.d_blocks, ncol, c.nproj, c.p.ns);
+  };
+  if (d_jobs) run(k_couple<T, true>);
+  else run(k_couple<T, false>);
+}
+template <typename T>
+void launch_sum_couple(const Ctx& c, const TailJob* d_jobs, int njob, const TailJob& one, int ncol, hipStream_t st) {
+  launch_slot_sum<T>(c, d_jobs, njob, one, ncol, st);
+  launch_couple_jobs<T>(c, d_jobs, njob, one, ncol, st);
+}
+template void launch_sum_couple<double>(const Ctx&, const TailJob*, int, const TailJob&, int, hipStream_t);
+template void launch_sum_couple<float>(const Ctx&, const TailJob*, int, const TailJob&, int, hipStream_t);
+template void launch_sum_couple<cplx<double>>(const Ctx&, const TailJob*, int, const TailJob&, int, hipStream_t);
+template void launch_sum_couple<cplx<float>>(const Ctx&, const TailJob*, int, const TailJob&, int, hipStream_t);
 
 template <typename T>
 bool scatter_project_ok(const Ctx& c) {
@@ -85,12 +134,7 @@ void launch_scatter_project(const Ctx& c, int ik, T* Y, int64_t ld, int ncol, co
   if constexpr (!std::is_same<T, cplx<double>>::value) {
     if (part_sel & 1)
       launch_brick_pass<T>(c, (const T*)c.d_bval[ik], (const T*)c.d_pbval[ik], Y, ld, ncol, Qt, alpha, true, true, st);
-    if (part_sel & 2) {
-      dim3 g2((ncol + 63) / 64, c.nproj);
-      launch_k(k_slot_sum<T>, g2, 1024, 0, st, (const T*)c.d_ppart, c.p.ns, ncol, c.d_jrow, P, c.nproj, c.dv);
-      dim3 g3((ncol + 63) / 64, (unsigned)c.blocks.size());
-      launch_k(k_couple<T>, g3, 64, 0, st, P, c.d_blocks, ncol, coup, Q, c.nproj, c.p.ns);
-    }
+    if (part_sel & 2) launch_sum_couple<T>(c, nullptr, 1, TailJob{c.d_ppart, P, Q, coup}, ncol, st);
   }
 }
 
@@ -153,26 +197,23 @@ size_t project_partial_elems(const Ctx& c) {
 template <typename T>
 void launch_project_table(const Ctx& c, const T* table, const T* Y, int ncol, int64_t ld, T* P, hipStream_t st) {
   if (c.nproj == 0) return;
-  T* part = reinterpret_cast<T*>(c.d_ppart);
   launch_brick_pass<T>(c, nullptr, table, const_cast<T*>(Y), ld, ncol, nullptr, 0.0, false, true, st);
-  dim3 g2((ncol + 63) / 64, c.nproj);
-  launch_k(k_slot_sum<T>, g2, 1024, 0, st, part, c.p.ns, ncol, c.d_jrow, P, c.nproj, c.dv);
+  launch_slot_sum<T>(c, nullptr, 1, TailJob{c.d_ppart, P, nullptr, nullptr}, ncol, st);
 }
 
 template <typename T>
 void launch_project_brick(const Ctx& c, int ik, const T* Y, int ncol, int64_t ld, const double* coup, T* P, T* Q,
                           hipStream_t st) {
   if (c.nproj == 0) return;
-  launch_project_table<T>(c, (const T*)c.d_pbval[ik], Y, ncol, ld, P, st);
-  dim3 g3((ncol + 63) / 64, (unsigned)c.blocks.size());
-  launch_k(k_couple<T>, g3, 64, 0, st, P, c.d_blocks, ncol, coup, Q, c.nproj, c.p.ns);
+  launch_brick_pass<T>(c, nullptr, (const T*)c.d_pbval[ik], const_cast<T*>(Y), ld, ncol, nullptr, 0.0, false, true,
+                       st);
+  launch_sum_couple<T>(c, nullptr, 1, TailJob{c.d_ppart, P, Q, coup}, ncol, st);
 }
 
 template <typename T>
 void launch_couple(const Ctx& c, const T* P, int ncol, const double* coup, T* Q, hipStream_t st) {
   if (c.nproj == 0) return;
-  dim3 g3((ncol + 63) / 64, (unsigned)c.blocks.size());
-  launch_k(k_couple<T>, g3, 64, 0, st, P, c.d_blocks, ncol, coup, Q, c.nproj, c.p.ns);
+  launch_couple_jobs<T>(c, nullptr, 1, TailJob{nullptr, const_cast<T*>(P), Q, coup}, ncol, st);
 }
 template void launch_couple<double>(const Ctx&, const double*, int, const double*, double*, hipStream_t);
 template void launch_couple<float>(const Ctx&, const float*, int, const double*, float*, hipStream_t);
