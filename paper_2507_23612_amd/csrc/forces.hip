@@ -161,13 +161,13 @@ constexpr int kBilin = 325;   // 25 (D) + 3 x 25 (forces) + 9 x 25 (stress) comp
 //   t <  25 : X = P,      Y = P        (occupation matrix of this (spin, k))
 //   t < 100 : X = P,      Y = G^a      (forces, a = (t - 25) / 25)
 //   t < 325 : X = Q^ab,   Y = P        (stress, 3a + b = (t - 100) / 25)
-// proj holds 13 arrays [ns][nproj] at multiples of pstride: P, G^0..2,
+// (sums 25 .. nskip - 1 are left zero).  proj holds 13 arrays [ns][nproj] at multiples of pstride: P, G^0..2,
 // Q^{ab} at 4 + 3a + b.
 template <typename T>
 __global__ __launch_bounds__(384) void k_hub_bilinear(const T* __restrict__ proj, int64_t pstride, int ns, int nproj,
                                                       const double* __restrict__ occ,
                                                       const BlockDesc* __restrict__ blocks,
-                                                      const int* __restrict__ hub_blocks, int nsum,
+                                                      const int* __restrict__ hub_blocks, int nskip, int nsum,
                                                       double* __restrict__ out) {
   using R = typename real_of<T>::type;
   const BlockDesc b = blocks[hub_blocks[blockIdx.x]];
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(384) void k_hub_bilinear(const T* __restrict__ proj
   else { xi = 4 + (t - 100) / 25; yi = 0; e = (t - 100) % 25; }
   const int m = e / 5, mp = e % 5;
   double re = 0, im = 0;
-  if (t < nsum && m < b.nm && mp < b.nm) {
+  if (t < nsum && (t < 25 || t >= nskip) && m < b.nm && mp < b.nm) {
     const T* __restrict__ X = proj + xi * pstride + b.j0 + m;
     const T* __restrict__ Y = proj + yi * pstride + b.j0 + mp;
     for (int s = 0; s < ns; ++s) {
@@ -245,13 +245,14 @@ hcu_status forces_stress_t(Ctx& c, const double* occ_host, double* forces, doubl
       launch_grad3<T>(X, nd, Gr, nd, ns, gc, st);
       const T* tab = (const T*)c.d_pbval[ik];
       launch_project_table<T>(c, tab, X, ns, nd, PR, st);
-      for (int a = 0; a < 3; ++a) launch_project_table<T>(c, tab, Gr[a], ns, nd, PR + (1 + a) * pstride, st);
+      if (forces)   // (the stress needs the moment functions' projections only)
+        for (int a = 0; a < 3; ++a) launch_project_table<T>(c, tab, Gr[a], ns, nd, PR + (1 + a) * pstride, st);
       if (want_stress)
         for (int a = 0; a < 3; ++a)
           for (int b = 0; b < 3; ++b)
             launch_project_table<T>(c, (const T*)c.d_mom[b], Gr[a], ns, nd, PR + (4 + 3 * a + b) * pstride, st);
       launch_k(k_hub_bilinear<T>, nh, 384, 0, st, (const T*)PR, pstride, ns, c.nproj, occ + (size_t)sk * ns,
-               c.d_blocks, c.d_hub_blocks, nsum, c.d_fsum);
+               c.d_blocks, c.d_hub_blocks, forces ? 25 : 100, nsum, c.d_fsum);
       HCU_HIP(hipGetLastError());
       HCU_HIP(hipMemcpyAsync(sums.data() + (size_t)sk * nh * kBilin * 2, c.d_fsum,
                              sizeof(double) * nh * kBilin * 2, hipMemcpyDeviceToHost, st));
