@@ -72,8 +72,15 @@ __host__ __device__ BrickArgs<T> brick_args(void* Y, int64_t ld, int ncol, const
 constexpr int kChunkFns = 16;                     // functions (slots) of one staged chunk
 constexpr int kChunkVals = kChunkFns * kBrick;
 template <typename T> constexpr int kTileRow = kBrick + kPack<T>;   // values of one state in the transposition tile
-template <typename T, bool PR>
-constexpr int kBrickLds = (2 * kChunkVals + (PR ? 4 * 16 * kTileRow<T> : 0)) * (int)sizeof(T);
+// A projection alone may load its values in the order in which the product
+// takes them (lane (n, q): state n, points 4 i + q) instead of transposing
+// them.  Done for 16-byte values, whose tile would leave room for one
+// workgroup per compute unit: 112 instead of 121 us on 45x37x50, 75 states.
+// (Elsewhere a load then meets four lines per quad of lanes: FP64 0.37
+// instead of 0.33 ms on 72x72x96, 256 states.)
+template <typename T, bool SC> constexpr bool kDirect = !SC && sizeof(T) == 16;
+template <typename T, bool SC, bool PR>
+constexpr int kBrickLds = (2 * kChunkVals + (PR && !kDirect<T, SC> ? 4 * 16 * kTileRow<T> : 0)) * (int)sizeof(T);
 
 // Waves per SIMD that the registers are allotted for: what the accumulators
 // (a brick's values, as many requested ahead, NT slot tiles) leave room for.
@@ -130,6 +137,7 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
   using E = typename El<T>::E;
   using V = typename Mf<R>::V;
   constexpr int C = El<T>::C;
+  constexpr bool DIR = kDirect<T, SC>;
   constexpr int G = kPack<E>, NG = 16 / G, RS = kTileRow<E>;
   constexpr int NL = kChunkVals / (256 * G);   // packs of a chunk that a thread stages
   E* const ring = reinterpret_cast<E*>(lds);
@@ -159,7 +167,9 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
   // states past the last one repeat it (never stored)
   OFF voff[4];
   for (int r = 0; r < 4; ++r)
-    voff[r] = ((OFF)(min(s0 + q + 4 * r, a.ncol - 1) - min(s0, a.ncol - 1)) * (OFF)a.ld + (OFF)geo.off(n)) * (OFF)sizeof(E);
+    voff[r] = ((OFF)(min(s0 + (DIR ? n : q + 4 * r), a.ncol - 1) - min(s0, a.ncol - 1)) * (OFF)a.ld +
+               (OFF)geo.off(DIR ? q : n)) *
+              (OFF)sizeof(E);
   const int sq = min(s0 + (sizeof(R) == 8 ? n : n / 4 + 4 * (n % 4)), a.ncol - 1);   // the state of operand row n
   Glob<E>* const Yw = a.Y + (int64_t)min(s0, a.ncol - 1) * a.ld;
   auto at = [&](Glob<E>* base, OFF o) -> Glob<E>& {
@@ -183,29 +193,29 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
     *rem = geo.cube ? w : a.nd - p0;   // points left along x
     return p0;
   };
-  auto past = [&](int64_t rem, int pt) -> int64_t { return ((16 * pt + n) & (geo.cube ? (1 << geo.lx) - 1 : 63)) - (rem - 1); };
+  // first point of the loads of (tile pt, r), and the lane's point in them
+  auto first = [&](int pt, int r) { return DIR ? 16 * pt + 4 * r : 16 * pt; };
+  auto past = [&](int64_t rem, int pt, int r) -> int64_t {
+    return ((first(pt, r) + (DIR ? q : n)) & (geo.cube ? (1 << geo.lx) - 1 : 63)) - (rem - 1);
+  };
   auto load_brick = [&](int k) {
     if (!wave_ok) return;
     bool whole;
     int64_t rem;
     const int64_t p0 = place(k, &whole, &rem);
     if (whole) {
-      for (int pt = 0; pt < 4; ++pt) {
-        Glob<E>* const base = scalar_base(Yw + (p0 + geo.off(16 * pt)));
+      for (int pt = 0; pt < 4; ++pt)
         for (int r = 0; r < 4; ++r) {
-          const E v = at(base, voff[r]);
+          const E v = at(scalar_base(Yw + (p0 + geo.off(first(pt, r)))), voff[r]);
           for (int c = 0; c < C; ++c) pre[c][pt][r] = part_of(v, c);
         }
-      }
     } else {
-      for (int pt = 0; pt < 4; ++pt) {
-        const int64_t d = past(rem, pt);
-        Glob<E>* const base = Yw + (p0 + geo.off(16 * pt) - (d > 0 ? d : 0));   // outside: the last point, zeroed
+      for (int pt = 0; pt < 4; ++pt)
         for (int r = 0; r < 4; ++r) {
-          const E v = at(base, voff[r]);
+          const int64_t d = past(rem, pt, r);   // outside: the last point, zeroed
+          const E v = at(Yw + (p0 + geo.off(first(pt, r)) - (d > 0 ? d : 0)), voff[r]);
           for (int c = 0; c < C; ++c) pre[c][pt][r] = d > 0 ? R(0) : part_of(v, c);
         }
-      }
     }
   };
   auto store_brick = [&](int k) {
@@ -216,7 +226,7 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
       Glob<E>* const base = scalar_base(Yw + (p0 + geo.off(16 * pt)));
       if (full && whole) {
         for (int r = 0; r < 4; ++r) at(base, voff[r]) = value(pt, r);
-      } else if (past(rem, pt) <= 0) {
+      } else if (past(rem, pt, 0) <= 0) {
         for (int r = 0; r < 4; ++r)
           if (s0 + q + 4 * r < a.ncol) at(base, voff[r]) = value(pt, r);
       }
@@ -328,9 +338,11 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
             // include them otherwise)
             if (wave_ok) {
               if (SC && ns > 0) store_brick(k);
-              for (int pt = 0; pt < 4; ++pt)
-                for (int r = 0; r < 4; ++r) yw[(q + 4 * r) * RS + 16 * pt + n] = value(pt, r);
-              wave_lds_sync();
+              if constexpr (!DIR) {
+                for (int pt = 0; pt < 4; ++pt)
+                  for (int r = 0; r < 4; ++r) yw[(q + 4 * r) * RS + 16 * pt + n] = value(pt, r);
+                wave_lds_sync();
+              }
             }
             if (ns == 0 && fetch) load_brick(k + 1);   // (jvn is its list, as above)
           }
@@ -339,7 +351,10 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
             const E* __restrict__ w = ring + par * kChunkVals + lane * G;
             const E* __restrict__ y = yw + n * RS + G * q;
             for (int i = 0; i < NG; ++i) {
-              const Pack<E> f = ld_pack(w + i * (64 * G)), v = ld_pack(y + 4 * G * i);
+              const Pack<E> f = ld_pack(w + i * (64 * G));
+              Pack<E> v;
+              if constexpr (DIR) v.v[0] = value(i / 4, i % 4);
+              else v = ld_pack(y + 4 * G * i);
               for (int e = 0; e < G; ++e) {
                 for (int c = 0; c < C; ++c)
                   pacc[t][c] = Mf<R>::mfma(part_of(f.v[e], 0), part_of(v.v[e], c), pacc[t][c]);
@@ -391,7 +406,7 @@ __device__ __forceinline__ BrickItem brick_item(const BrickGeo& geo, unsigned lw
 template <typename T, typename OFF, int NT, bool SC, bool PR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBrickWaves<T, NT>))) void k_brick_pass(
     const BrickArgs<T> a, int nst, int per, const BrickGeo geo) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kBrickLds<T, PR>];
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kBrickLds<T, SC, PR>];
   const unsigned lw = xcd_linear();
   const BrickItem it = brick_item(geo, lw, nst);
   const int k0 = it.b * per;
@@ -403,7 +418,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBrickWaves
 template <typename T, typename OFF, int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBrickWaves<T, NT>))) void k_brick_pass_batch(
     const FusedJob* __restrict__ jobs, int njob) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kBrickLds<T, true>];
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kBrickLds<T, true, true>];
   const unsigned lw = xcd_linear();
   // (a copy in scalar registers: read before any store)
   FusedJob J;

@@ -36,7 +36,7 @@ def _cell(n, ns, k, copies):
 @pytest.mark.parametrize("precision,k", [("fp64", 0), ("mixed", 0), ("fp64", 1), ("mixed", 1)])
 @pytest.mark.parametrize("n,ns,pad,copies", [
     ((16, 16, 12), 17, 0, 1), ((20, 16, 9), 1, 3, 1), ((31, 12, 8), 15, 1, 1), ((11, 10, 9), 70, 5, 1),
-    ((16, 8, 8), 33, 0, 2), ((15, 8, 8), 16, 1, 4), ((13, 12, 10), 65, 0, 4)])
+    ((16, 8, 8), 33, 0, 2), ((23, 16, 9), 18, 0, 1), ((15, 8, 8), 16, 1, 4), ((13, 12, 10), 65, 0, 4)])
 def test_projector_pass(n, ns, pad, copies, precision, k):
     torch = _torch()
     from oracle import chfsi
