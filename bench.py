@@ -349,8 +349,8 @@ def fused_roofline(cfg, prec, sizes, kt, config, tile, complex_):
     peak_tf = MFMA_PEAK_TFLOPS["mixed" if prec == "mixed" else "fp64"]
     return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4),
-            "traffic": measured_traffic("k_scatter_project", config, prec, tile, ("proj.hip",)),
-            "kernel": "k_scatter_project (projector scatter of a Chebyshev step fused with the projections of "
+            "traffic": measured_traffic("k_brick_pass", config, prec, tile, ("bricks.hip",)),
+            "kernel": "k_brick_pass (projector scatter of a Chebyshev step fused with the projections of "
                       "its output)",
             "avg_launch_ms": round(ms, 4), "algorithmic_bytes_per_launch": int(nbytes),
             "algorithmic_flops_per_launch": int(flops), "achieved_tflops": round(tf, 2),
