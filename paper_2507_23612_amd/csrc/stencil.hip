@@ -171,6 +171,12 @@ template <typename T, int VX, int RY>
 constexpr int kStencilWaves = VX * RY * sizeof(T) <= 4 ? 8 : VX * RY * sizeof(T) <= 8 ? 5
                             : VX * RY * sizeof(T) <= 16 ? (sizeof(T) == 16 ? 3 : 4) : VX == 2 ? 3 : 2;
 
+// Real points that are not side by side in vectors take the queue form.
+template <typename T, int VX>
+constexpr bool kQueue = VX == 1 && std::is_arithmetic<T>::value;
+template <typename T, int VX, int RY>
+constexpr int kWaves = kQueue<T, VX> ? 2 : kStencilWaves<T, VX, RY>;
+
 // One work item: tile `tile` of the x-y plane, z chunk `zc`, state `s`.
 //
 // What bounds it: HBM streaming (3 words per point) as long as the y/x halo of
@@ -435,9 +441,144 @@ __device__ __forceinline__ void stencil_item(const T* __restrict__ Yin, const T*
   }
 }
 
+// The same work item for real points without vectors (rows of odd length, or
+// one point per thread): the 2R + 1 z neighbours of a thread's points wait in
+// a register queue and one pass over the plane forms the sum.  Without vectors
+// the forward sum's LDS reads are one point each as well, and its second pass
+// over them costs more than the halo rows it finds in L2: 63x63x41, 192
+// states, 145 us (FP32) and 272 us (FP64) in the queue, 268 and 401 forwards;
+// with vectors (64x62x40) 76 and 152 us forwards, 111 and 206 in the queue.
+//
+// FP32 tiles of odd checkerboard parity sweep their z range R planes behind
+// the even ones (periodic in z), so that their own reads of a plane coincide
+// with the neighbours' halo reads of it (9 % fewer bytes fetched).
+template <typename T, int R, int RY, int NHS>
+__device__ __forceinline__ void queue_item(const T* __restrict__ Yin, const T* __restrict__ Yprev, T* __restrict__ Yout,
+                                           const T* __restrict__ V, const KArgs<T>& a, int tile, int zc, int64_t s,
+                                           unsigned char* smem_raw) {
+  using GC = const __attribute__((address_space(1))) T*;
+  using GT = __attribute__((address_space(1))) T*;
+  const int TX = blockDim.x, TYt = blockDim.y, TY = TYt * RY;
+  const int SW = TX + 2 * R, SH = TY + 2 * R;
+  T* const buf0 = reinterpret_cast<T*>(smem_raw);
+  T* const buf1 = buf0 + SW * SH;
+  const int tx = threadIdx.x, ty = threadIdx.y;
+  const int tid = ty * TX + tx, nthr = TX * TYt;
+  const int bx = tile % a.tiles_x, by = tile / a.tiles_x;
+  const int x0 = bx * TX, y0 = by * TY;
+  const int zbeg = zc * a.tz, zend = min(zbeg + a.tz, a.n3);
+  const int n1 = a.n1, n2 = a.n2, n3 = a.n3;
+  const int zsh = (sizeof(T) == 4 && ((bx + by) & 1) && n3 > R) ? n3 - R : 0;
+  const GC Ys = (GC)(Yin + s * a.ld), Yp = (GC)(a.has_prev ? Yprev + s * a.ld_prev : Yin + s * a.ld), Vg = (GC)V;
+  const GT Yo = (GT)(Yout + s * a.ld_out);
+  const int64_t plane = (int64_t)n1 * n2;
+  const bool xfull = (TX == n1) && (n1 >= R);   // x halo from the staged row itself
+  int w;
+  const int gx = wrap(x0 + tx, n1, w);
+  int gy[RY];
+  for (int r = 0; r < RY; ++r) gy[r] = wrap(y0 + ty * RY + r, n2, w);
+  // halo values of this thread: y halo (2R rows x TX) then, unless xfull, x
+  // halo (TY rows x 2R); unused slots read node 0 and stage nothing
+  const int nyh = 2 * R * TX, nh = nyh + (xfull ? 0 : TY * 2 * R);
+  int h_xy[NHS], h_lds[NHS];
+  for (int k = 0; k < NHS; ++k) {
+    const int e = tid + k * nthr;
+    h_lds[k] = -1;
+    h_xy[k] = 0;
+    if (e >= nh) continue;
+    int row, col;
+    if (e < nyh) {
+      const int rh = e / TX;
+      col = e % TX + R;
+      row = rh < R ? rh : TY + rh;
+    } else {
+      const int e2 = e - nyh, cc = e2 % (2 * R);
+      row = e2 / (2 * R) + R;
+      col = cc < R ? cc : TX + cc;
+    }
+    h_lds[k] = row * SW + col;
+    h_xy[k] = wrap(x0 + col - R, n1, w) + n1 * wrap(y0 + row - R, n2, w);
+  }
+  T q[RY][2 * R + 1];
+  for (int dz = -R; dz <= R; ++dz) {
+    const int gz = wrap(zbeg + zsh + dz, n3, w);
+    for (int r = 0; r < RY; ++r) q[r][dz + R] = Ys[gx + (int64_t)n1 * gy[r] + plane * gz];
+  }
+  auto stage = [&](T* buf, const T* hreg) {
+    for (int r = 0; r < RY; ++r) {
+      const int row = ty * RY + r + R;
+      const T v = q[r][R];
+      buf[row * SW + tx + R] = v;
+      if (xfull) {
+        if (tx < R) buf[row * SW + tx + n1 + R] = v;
+        if (tx >= n1 - R) buf[row * SW + tx - n1 + R] = v;
+      }
+    }
+    for (int k = 0; k < NHS; ++k)
+      if (h_lds[k] >= 0) buf[h_lds[k]] = hreg[k];
+  };
+  T hreg[NHS];
+  {
+    const int gz = wrap(zbeg + zsh, n3, w);
+    for (int k = 0; k < NHS; ++k) hreg[k] = Ys[h_xy[k] + plane * gz];
+    stage(buf0, hreg);
+  }
+  __syncthreads();
+  int cur = 0;
+  for (int z = zbeg; z < zend; ++z) {
+    const bool more = z + 1 < zend;
+    T qn[RY];   // the next plane's queue head and halo, this plane's V and yprev
+    if (more) {
+      const int gz = wrap(z + 1 + R + zsh, n3, w), zh = wrap(z + 1 + zsh, n3, w);
+      for (int r = 0; r < RY; ++r) qn[r] = Ys[gx + (int64_t)n1 * gy[r] + plane * gz];
+      for (int k = 0; k < NHS; ++k) hreg[k] = Ys[h_xy[k] + plane * zh];
+    }
+    const int64_t zoff = plane * (z + zsh - (z + zsh >= n3 ? n3 : 0));
+    T vv[RY], yp[RY];
+    for (int r = 0; r < RY; ++r) {
+      const int64_t p = gx + (int64_t)n1 * gy[r] + zoff;
+      vv[r] = Vg[p];
+      yp[r] = T(0);
+      if (a.has_prev) yp[r] = Yp[p];
+    }
+    const T* B = cur ? buf1 : buf0;
+    for (int r = 0; r < RY; ++r) {
+      const T* L = B + (ty * RY + r + R) * SW + tx + R;
+      T acc = (a.center + a.alpha * vv[r]) * q[r][R];
+      for (int p = 1; p <= R; ++p) {
+        acc += a.kx[p] * (L[p] + L[-p]);
+        // y neighbours inside the thread's own rows come from the queue
+        const T up = (r + p < RY) ? q[(r + p) % RY][R] : L[p * SW];
+        const T dn = (r - p >= 0) ? q[(r - p + RY) % RY][R] : L[-p * SW];
+        acc += a.ky[p] * (up + dn);
+        acc += a.kz[p] * (q[r][R + p] + q[r][R - p]);
+      }
+      if ((x0 + tx < n1) && (y0 + ty * RY + r < n2)) {
+        if (a.has_prev) acc += (-a.beta) * yp[r];
+        Yo[gx + (int64_t)n1 * gy[r] + zoff] = acc;
+      }
+    }
+    for (int r = 0; r < RY; ++r) {
+      for (int t = 0; t < 2 * R; ++t) q[r][t] = q[r][t + 1];
+      if (more) q[r][2 * R] = qn[r];
+    }
+    if (more) stage(cur ? buf0 : buf1, hreg);
+    __syncthreads();
+    cur ^= 1;
+  }
+}
+
+template <typename T, typename RT, int R, int VX, int RY, int NHS>
+__device__ __forceinline__ void run_item(const T* __restrict__ Yin, const T* __restrict__ Yprev, T* __restrict__ Yout,
+                                         const RT* __restrict__ V, const KArgs<RT>& a, int tile, int zc, int64_t s,
+                                         unsigned char* smem_raw) {
+  if constexpr (kQueue<T, VX>) queue_item<T, R, RY, NHS>(Yin, Yprev, Yout, V, a, tile, zc, s, smem_raw);
+  else stencil_item<T, RT, R, VX, RY, NHS>(Yin, Yprev, Yout, V, a, tile, zc, s, smem_raw);
+}
+
 template <typename T, typename RT, int R, int VX, int RY, int NHS>
 __global__ __launch_bounds__((kStencilThreads<T, RT, VX * RY>))
-__attribute__((amdgpu_waves_per_eu(kStencilWaves<T, VX, RY>))) void k_stencil(const T* __restrict__ Yin,
+__attribute__((amdgpu_waves_per_eu(kWaves<T, VX, RY>))) void k_stencil(const T* __restrict__ Yin,
                                                                           const T* __restrict__ Yprev,
                                                                           T* __restrict__ Yout,
                                                                           const RT* __restrict__ V,
@@ -448,7 +589,7 @@ __attribute__((amdgpu_waves_per_eu(kStencilWaves<T, VX, RY>))) void k_stencil(co
   const int tile = lw % gridDim.x;
   const int zc = (lw / gridDim.x) % gridDim.y;
   const int64_t s = lw / (gridDim.x * gridDim.y);
-  stencil_item<T, RT, R, VX, RY, NHS>(Yin, Yprev, Yout, V, a, tile, zc, s, smem_raw);
+  run_item<T, RT, R, VX, RY, NHS>(Yin, Yprev, Yout, V, a, tile, zc, s, smem_raw);
 }
 
 // Form over a list of jobs (blocks of possibly different grids): one workgroup
@@ -457,7 +598,7 @@ __attribute__((amdgpu_waves_per_eu(kStencilWaves<T, VX, RY>))) void k_stencil(co
 // balances.
 template <typename T, typename RT, int R, int VX, int RY, int NHS>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(kStencilWaves<T, VX, RY>))) void k_stencil_multi(const SJob<RT>* __restrict__ jobs, int njobs) {
+__attribute__((amdgpu_waves_per_eu(kWaves<T, VX, RY>))) void k_stencil_multi(const SJob<RT>* __restrict__ jobs, int njobs) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const unsigned long long item = xcd_linear();
   int lo = 0, hi = njobs - 1;
@@ -471,7 +612,7 @@ __attribute__((amdgpu_waves_per_eu(kStencilWaves<T, VX, RY>))) void k_stencil_mu
   const int tile = (int)(loc % jb.ntiles);
   const int zc = (int)((loc / jb.ntiles) % jb.nzc);
   const int64_t s = (int64_t)(loc / ((unsigned long long)jb.ntiles * jb.nzc));
-  stencil_item<T, RT, R, VX, RY, NHS>((const T*)jb.Yin, (const T*)jb.Yprev, (T*)jb.Yout, jb.V, jb.a, tile, zc, s, smem_raw);
+  run_item<T, RT, R, VX, RY, NHS>((const T*)jb.Yin, (const T*)jb.Yprev, (T*)jb.Yout, jb.V, jb.a, tile, zc, s, smem_raw);
 }
 
 // Tile shape for a grid: TX threads along x, TYt thread rows, RY points per
@@ -537,6 +678,8 @@ bool stencil_shape_ok(const Ctx& c, int TX, int TYt, int RY, int tz, int ring) {
 // z until there are three per CU (c1, 32 states: 10.3 us with 768 workgroups
 // of 3 planes, 34 us with 128 of 12).  Sixteen-byte values take one point per
 // thread (their sums fill the registers), rows without whole vectors two.
+static constexpr bool vectors_built(int R) { return R == 4 || R == kMaxR; }
+
 static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
   const int n1 = c.p.n[0], n2 = c.p.n[1], n3 = c.p.n[2];
   const int R = c.p.n0;
@@ -548,10 +691,11 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
     const int TY = sh.TYt * sh.RY;
     return (int64_t)((n1 + sh.TX - 1) / sh.TX) * ((n2 + TY - 1) / TY);
   };
+  const bool vectors = vectors_built(R) && n1 % 2 == 0 && sh.TX % 2 == 0, queue = !vectors && !c.any_complex;
   auto set_rows = [&](int ry) {
     sh.RY = ry;
     while (sh.RY > 1 && sh.RY > n2) sh.RY /= 2;
-    sh.TYt = std::max(1, std::min(256 / sh.TX, n2 / sh.RY));
+    sh.TYt = std::max(1, std::min((queue && elem == 4 && sh.TX > 64 ? 512 : 256) / sh.TX, n2 / sh.RY));
     // few rows on a narrow grid: single rows keep enough threads for the halo
     if (halo_slots(n1, sh.TX, sh.TYt, sh.TYt * sh.RY, R) > kHaloSlots) {
       sh.RY = 1;
@@ -559,7 +703,9 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
     }
   };
   sh.tz = n3;
-  set_rows(elem > 8 ? 1 : R == kMaxR && n1 % 2 == 0 && sh.TX % 2 == 0 ? 4 : 2);
+  // (99x99x85, 608 states, FP32 in a queue: 2 rows of 4 points 1.95 ms, 5 rows
+  // 1.64; 63x63x41, FP64: 4 points 333 us, 2 points 257)
+  set_rows(elem > 8 ? 1 : vectors ? 4 : queue && elem == 4 ? 4 : 2);
   if (tiles() * ncol < 512) {
     if (sh.RY > 2) set_rows(2);
     int zs = 1;
@@ -579,10 +725,11 @@ static void allow_lds(K kernel, size_t lds) {
 // The points of a thread (PT of them, a shape's ry) lie side by side in x
 // where the rows allow whole vectors, else stacked in y.  One vector access
 // then moves up to 16 bytes of LDS and memory per lane, and the x neighbours
-// of a vector overlap.  Built for the order-12 stencil.
+// of a vector overlap.  Built for the orders 8 and 12 (the halo slots count on x
+// margins of R rounded to whole vectors no further than that).
 template <typename T>
 static int vector_points(int R, int PT, int n1, int TX) {
-  if (R != kMaxR) return 1;
+  if (!vectors_built(R)) return 1;
   int vx = std::min(PT, (int)(16 / sizeof(T)));
   while (n1 % vx || TX % vx) vx /= 2;
   return vx;
@@ -598,7 +745,7 @@ static void for_variant(int PT, int vx, bool small, F f) {
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I4 = std::integral_constant<int, 4>;
-  if constexpr (R == kMaxR && sizeof(T) <= 8) {
+  if constexpr (vectors_built(R) && sizeof(T) <= 8) {
     if (vx == 2) return PT == 4 ? slots(I2(), I2()) : slots(I2(), I1());
     if constexpr (sizeof(T) == 4)
       if (vx == 4) return slots(I4(), I1());

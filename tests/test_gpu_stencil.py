@@ -35,7 +35,8 @@ def _bare(n, ns, n0, k):
 @pytest.mark.parametrize("n,precision,k,n0", [
     ((20, 18, 14), "fp64", 0, 6), ((22, 16, 11), "mixed", 0, 6), ((64, 30, 7), "mixed", 0, 6),
     ((21, 17, 9), "fp64", 0, 6), ((20, 18, 14), "fp64", 1, 6), ((22, 16, 11), "mixed", 1, 6),
-    ((13, 11, 10), "mixed", 1, 4), ((7, 6, 5), "fp64", 0, 6)])
+    ((13, 11, 10), "mixed", 1, 4), ((7, 6, 5), "fp64", 0, 6), ((23, 21, 9), "mixed", 0, 6), ((19, 16, 8), "fp64", 0, 4),
+    ((20, 18, 14), "mixed", 0, 4), ((20, 18, 14), "fp64", 0, 5), ((16, 14, 9), "mixed", 0, 3), ((18, 14, 9), "mixed", 1, 1)])
 def test_stencil_shapes(n, precision, k, n0):
     torch = _torch()
     from oracle import chfsi
@@ -74,8 +75,9 @@ def test_stencil_shapes(n, precision, k, n0):
 
 @pytest.mark.parametrize("precision,k", [("fp64", 0), ("mixed", 0), ("mixed", 1)])
 def test_stencil_points_per_thread_agree_on_a_full_chip(precision, k):
-    """Enough states to fill the device: one, two and four points per thread
-    sum in the same order, so they agree to the last bit."""
+    """Enough states to fill the device: two and four points per thread sum in
+    the same order, so they agree to the last bit, and single complex points
+    too (single real points are summed in another order: 1e-13 / 1e-5)."""
     torch = _torch()
     from paper_2507_23612_amd import hcu
     cfg = _bare((72, 72, 24), 192, 6, k)
@@ -83,12 +85,15 @@ def test_stencil_points_per_thread_agree_on_a_full_chip(precision, k):
     g = torch.Generator(device="cuda").manual_seed(4)
     X = torch.randn((192, ctx.nd), generator=g, device="cuda", dtype=torch.float64).to(ctx.dtype)
     Y, ref = torch.empty_like(X), None
-    for shape in ((72, 3, 1, 24), (72, 3, 2, 24), (72, 3, 4, 24), (36, 6, 4, 24), (32, 8, 4, 12)):
+    for shape in ((72, 3, 2, 24), (72, 3, 4, 24), (36, 6, 4, 24), (32, 8, 4, 12), (72, 3, 1, 24), (36, 6, 1, 7)):
         ctx.set_tuning(*shape)
         for _ in range(2):
             Y.fill_(float("nan"))
             ctx.cheb_filter(X, Y, 3, 20.0, 190.0, -1.0)
             if ref is None:
                 ref = Y.clone()
-            assert torch.equal(Y, ref), shape
+            if shape[2] == 1 and not k:
+                assert float((Y - ref).abs().max() / ref.abs().max()) < (1e-13 if precision == "fp64" else 1e-5), shape
+            else:
+                assert torch.equal(Y, ref), shape
     ctx.close()
