@@ -97,3 +97,25 @@ def test_stencil_points_per_thread_agree_on_a_full_chip(precision, k):
             else:
                 assert torch.equal(Y, ref), shape
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [(36, 36, 24), (35, 33, 26)])
+@pytest.mark.parametrize("k,n0", [(0, 6), (1, 6), (0, 4), (1, 4)])
+def test_stencil_fp32_error(n, k, n0):
+    """Rounding of one FP32 application to random blocks.  On random values the
+    centre term makes most of the result, so only the centre and the n0 planes
+    added after it round at the result's size; the neighbour sums (0.43 of it,
+    most of that from the last two terms) and the rounded weights count as five
+    more.  A rounding is 2.5e-8 rms of the value it is made at."""
+    torch = _torch()
+    from oracle.hamiltonian import Hamiltonian
+    from paper_2507_23612_amd import hcu
+    cfg = _bare(n, 8, n0, k)
+    ctx = hcu.HcuContext(cfg, "mixed")
+    X = torch.from_numpy(workloads.random_block(ctx.nd, 8, 7, bool(k))).cuda().to(ctx.dtype)
+    Y = torch.empty_like(X)
+    ctx.apply_h(X, Y)
+    want = Hamiltonian(cfg, cfg["kpts"][0]).apply(X.cpu().numpy().astype(np.complex128 if k else np.float64))
+    err = np.linalg.norm(Y.cpu().numpy() - want) / np.linalg.norm(want)
+    ctx.close()
+    assert err < 2.5e-8 * np.sqrt(n0 + 6), err
