@@ -105,7 +105,7 @@ size_t layout(Ctx& c, char* base, bool assign = true) {
   b.take(c.d_red, red);
   b.take(c.d_scal, sizeof(double) * (64 + nsk + nh + c.p.nspin + 8));
   b.take(c.d_rho, sizeof(double) * (size_t)c.p.nspin * c.nd);
-  b.take(c.d_vec, es * (size_t)c.nd * 4);
+  b.take(c.d_vec, es * (size_t)c.nd * (c.mixed ? 8 : 4));   // (FP32 blocks: three vectors of doubles, two of floats)
   b.take(c.d_lowC, sizeof(double) * 50 * (size_t)c.p.nk * nh);
   b.take(c.d_fproj, es * 13 * (size_t)ns * c.nproj);
   b.take(c.d_fsum, sizeof(double) * 650 * (size_t)nh);
@@ -853,20 +853,31 @@ template <typename T>
 hcu_status lanczos_t(Ctx& c, int spin, int ik, int steps, double* th_min, double* upper) {
   const int sk = sk_index(c, spin, ik);
   const int64_t nd = c.nd;
-  T* v = (T*)c.d_vec;
-  T* w = v + nd;
-  T* vp = w + nd;
+  using D = double_of<T>;
+  constexpr bool same = std::is_same<D, T>::value;
+  D* const v = (D*)c.d_vec;
+  T* const v32 = (T*)(v + 3 * nd);
+  LanczosVec<D, T> z{v, v + nd, v + 2 * nd, same ? nullptr : v32, same ? nullptr : v32 + nd};
   // scalars of up to 24 steps at a time stay on the device: d_scal[8] = |v0|,
   // [9] = the last beta, [16 ..] = alpha, [40 ..] = beta
   constexpr int kBatch = 24;
   double* const sc = c.d_scal;
-  launch_lanczos_start<T>(c, (const T*)c.d_v0[sk], v, vp, sc + 8, c.stream);
+  launch_lanczos_start<D, T>(c, (const T*)c.d_v0[sk], z, sc + 8, c.stream);
   std::vector<double> al, be;
   for (int j0 = 0; j0 < steps && (be.empty() || be.back() != 0.0); j0 += kBatch) {
     const int m = std::min(kBatch, steps - j0);
     for (int j = 0; j < m; ++j) {
-      apply_h_t<T>(c, spin, ik, v, nd, w, nd, 1);
-      launch_lanczos_step<T>(c, v, vp, w, j0 + j == 0, sc + 16 + j, sc + 40 + j, sc + 9, c.stream);
+      if constexpr (same) {
+        apply_h_t<T>(c, spin, ik, z.v, nd, z.w, nd, 1);
+      } else {
+        if (c.nproj > 0) project_t<T>(c, spin, ik, z.v32, nd, 1);
+        {
+          ProfScope ps(c, PK_STENCIL);
+          launch_stencil<D>(c, ik, z.v, nd, nullptr, 0, z.w, nd, 1, 1.0, 0.0, 0.0, c.stream);
+        }
+        if (c.nproj > 0) scatter_t<T>(c, spin, ik, z.u, nd, 1, 1.0);
+      }
+      launch_lanczos_step<D, T>(c, z, j0 + j == 0, sc + 16 + j, sc + 40 + j, sc + 9, c.stream);
     }
     HCU_HIP(hipGetLastError());
     double host[64];

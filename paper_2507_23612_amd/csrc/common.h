@@ -8,6 +8,7 @@
 
 #include <cstdint>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/hubbard_chfsi.h"
@@ -34,6 +35,9 @@ template <typename R> __host__ __device__ inline cplx<R>& operator+=(cplx<R>& a,
 
 template <typename T> struct real_of { using type = T; };
 template <typename R> struct real_of<cplx<R>> { using type = R; };
+// the same kind of number in double precision
+template <typename T> using double_of =
+    typename std::conditional<std::is_arithmetic<T>::value, double, cplx<double>>::type;
 
 template <typename T> __host__ __device__ inline T conj_(T a) { return a; }
 template <typename R> __host__ __device__ inline cplx<R> conj_(cplx<R> a) { return {a.re, -a.im}; }
@@ -267,7 +271,7 @@ struct Ctx {
   double* d_scal = nullptr;          // scalars [0..63]: mu, e_band, dc, E_U, kT S, F, dot results;
                                      // then kw per (spin,k), U per Hubbard atom, coupling pointers
   double* d_rho = nullptr;           // density [nspin][nd]
-  void* d_vec = nullptr;             // Lanczos work vectors (4 x nd)
+  void* d_vec = nullptr;             // Lanczos work vectors (4 x nd; FP32 blocks: 8 x nd)
   // state
   std::vector<double> D_in;          // [nspin][nhub][25]
   std::vector<double> bounds;        // per (spin,k): a, b, aL
@@ -565,10 +569,17 @@ template <typename T>
 void launch_rotate_proj(const Ctx& c, const T* PY, const T* Cb, T* PX, int ncol, hipStream_t st);
 
 // scf_kernels.hip
-template <typename T>
-void launch_lanczos_start(const Ctx& c, const T* v0, T* v, T* vp, double* norm, hipStream_t st);
-template <typename T>
-void launch_lanczos_step(const Ctx& c, T* v, T* vp, T* w, bool first, double* alpha, double* beta, double* carry,
+// Vectors of a Lanczos recursion, in double precision (D) for blocks of T;
+// v32, u: copy of v and projector term in T for FP32 blocks, else null
+template <typename D, typename T>
+struct LanczosVec {
+  D *v, *w, *vp;
+  T *v32, *u;
+};
+template <typename D, typename T>
+void launch_lanczos_start(const Ctx& c, const T* v0, const LanczosVec<D, T>& z, double* norm, hipStream_t st);
+template <typename D, typename T>
+void launch_lanczos_step(const Ctx& c, LanczosVec<D, T>& z, bool first, double* alpha, double* beta, double* carry,
                          hipStream_t st);
 template <typename T>
 void launch_convert_c(const double* C, T* Cb, int n, int cplx, hipStream_t st);

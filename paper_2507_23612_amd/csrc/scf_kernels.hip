@@ -8,6 +8,8 @@
 // E_U = sum_sigma sum_I U/2 Tr(D - D^2) (Eq. E_U).
 #include "common.h"
 
+#include <utility>
+
 namespace hcu {
 
 __device__ inline double block_sum(double v, double* sh) {
@@ -29,94 +31,139 @@ __device__ inline double block_sum(double v, double* sh) {
 // and nothing waits for the host.  (Scalars on the host, two round trips and
 // ten launches and copies per step: the 10-step bound of one 36x36x24 block
 // took 1.20 ms, 0.55 ms of it idle; this 0.49 ms.)
+//
+// The vectors v, w, vp are doubles (D) for FP32 blocks (T) too: the lowest
+// Ritz value is what is left when terms of the upper bound's size cancel, and
+// rounding the vectors to 32 bits leaves it 8e-7 off (rms of 120 cells of 6 to
+// 108 atoms, single ones 2e-6).  Only the projector term is computed in T,
+// from the copy v32 of v into u, which joins w in the sums: 7e-9 off, in the
+// same time (36x36x24 0.45 ms).
 constexpr int kLzParts = 256;
 
-// part[b] = workgroup b's share of Re sum conj(x) y
-template <typename T>
-__global__ __launch_bounds__(256) void k_lz_dot(const T* __restrict__ x, const T* __restrict__ y, int64_t n,
-                                                double* __restrict__ part) {
+__device__ inline double lz_re(double x) { return x; }
+__device__ inline double lz_re(cplx<double> x) { return x.re; }
+template <typename D, typename T>
+__device__ inline D lz_widen(T x) {
+  if constexpr (std::is_arithmetic<T>::value) return (D)x;
+  else return D((double)x.re, (double)x.im);
+}
+template <typename T, typename D>
+__device__ inline T lz_narrow(D x) {
+  if constexpr (std::is_arithmetic<T>::value) return (T)x;
+  else return T((typename real_of<T>::type)x.re, (typename real_of<T>::type)x.im);
+}
+
+// part[b] = workgroup b's share of Re sum conj(x) (y + u)
+template <typename D, typename T>
+__global__ __launch_bounds__(256) void k_lz_dot(const D* __restrict__ x, const D* __restrict__ y,
+                                                const T* __restrict__ u, int64_t n, double* __restrict__ part) {
   __shared__ double sh[256];
   double re = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
-    const T p = mul_conj(y[i], x[i]);
-    if constexpr (sizeof(T) == sizeof(typename real_of<T>::type)) re += (double)p;
-    else re += (double)p.re;
+    D z = y[i];
+    if (u) z += lz_widen<D>(u[i]);
+    re += lz_re(mul_conj(z, x[i]));
   }
   re = block_sum(re, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = re;
 }
 
-// v = v0 / |v0|, vp = 0; *norm = |v0| from the partial sums of v0.v0
-template <typename T>
-__global__ __launch_bounds__(256) void k_lz_start(const T* __restrict__ v0, T* __restrict__ v, T* __restrict__ vp,
-                                                  int64_t n, const double* __restrict__ part, double* norm) {
+// part[b] = workgroup b's share of |x|^2
+template <typename D, typename T>
+__global__ __launch_bounds__(256) void k_lz_norm(const T* __restrict__ x, int64_t n, double* __restrict__ part) {
+  __shared__ double sh[256];
+  double re = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
+    const D z = lz_widen<D>(x[i]);
+    re += lz_re(mul_conj(z, z));
+  }
+  re = block_sum(re, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = re;
+}
+
+// v = v0 / |v0|, vp = 0, v32 = v, u = 0; *norm = |v0| from its partial sums
+template <typename D, typename T>
+__global__ __launch_bounds__(256) void k_lz_start(const T* __restrict__ v0, D* __restrict__ v, D* __restrict__ vp,
+                                                  T* __restrict__ v32, T* __restrict__ u, int64_t n,
+                                                  const double* __restrict__ part, double* norm) {
   __shared__ double sh[256];
   const double nrm = sqrt(block_sum(part[threadIdx.x], sh));
   if (blockIdx.x == 0 && threadIdx.x == 0) *norm = nrm;
-  const auto f = (typename real_of<T>::type)(1.0 / nrm);
+  const double f = 1.0 / nrm;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
-    v[i] = f * v0[i];
-    vp[i] = T(0);
+    const D x = f * lz_widen<D>(v0[i]);
+    v[i] = x;
+    vp[i] = D(0);
+    if (v32) {
+      v32[i] = lz_narrow<T>(x);
+      u[i] = T(0);
+    }
   }
 }
 
-// *alpha = the scalar product in part; w -= alpha v, then w -= *bprev vp
+// *alpha = the scalar product in part; w += u - alpha v, then w -= *bprev vp
 // (bprev null: the first step); part2 = partial sums of w.w
-template <typename T>
-__global__ __launch_bounds__(256) void k_lz_orth(T* __restrict__ w, const T* __restrict__ v, const T* __restrict__ vp,
-                                                 int64_t n, const double* __restrict__ part, double* alpha,
-                                                 const double* bprev, double* __restrict__ part2) {
+template <typename D, typename T>
+__global__ __launch_bounds__(256) void k_lz_orth(D* __restrict__ w, const T* __restrict__ u, const D* __restrict__ v,
+                                                 const D* __restrict__ vp, int64_t n, const double* __restrict__ part,
+                                                 double* alpha, const double* bprev, double* __restrict__ part2) {
   __shared__ double sh[256];
   const double al = block_sum(part[threadIdx.x], sh);
   if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = al;
-  const T a = make_scalar<T>(-al, 0.0), b = make_scalar<T>(bprev ? -*bprev : 0.0, 0.0);
+  const D a = make_scalar<D>(-al, 0.0), b = make_scalar<D>(bprev ? -*bprev : 0.0, 0.0);
   double re = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
-    T x = w[i];
+    D x = w[i];
+    if (u) x += lz_widen<D>(u[i]);
     x += a * v[i];
     if (bprev) x += b * vp[i];
     w[i] = x;
-    const T p = mul_conj(x, x);
-    if constexpr (sizeof(T) == sizeof(typename real_of<T>::type)) re += (double)p;
-    else re += (double)p.re;
+    re += lz_re(mul_conj(x, x));
   }
   re = block_sum(re, sh);
   if (threadIdx.x == 0) part2[blockIdx.x] = re;
 }
 
-// *beta = *carry = |w| from part2; vp = v, v = w / beta (beta = 0, the end of
-// the recursion: left alone)
-template <typename T>
-__global__ __launch_bounds__(256) void k_lz_next(T* __restrict__ v, T* __restrict__ vp, const T* __restrict__ w,
-                                                 int64_t n, const double* __restrict__ part2, double* beta,
-                                                 double* carry) {
+// *beta = *carry = |w| from part2; w /= beta, the next v (the buffers change
+// places); v32 = w, u = 0 (beta = 0, the end of the recursion: left alone)
+template <typename D, typename T>
+__global__ __launch_bounds__(256) void k_lz_next(D* __restrict__ w, T* __restrict__ v32, T* __restrict__ u, int64_t n,
+                                                 const double* __restrict__ part2, double* beta, double* carry) {
   __shared__ double sh[256];
   const double be = sqrt(block_sum(part2[threadIdx.x], sh));
   if (blockIdx.x == 0 && threadIdx.x == 0) *beta = *carry = be;
   if (be == 0.0) return;
-  const auto f = (typename real_of<T>::type)(1.0 / be);
+  const double f = 1.0 / be;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
-    vp[i] = v[i];
-    v[i] = f * w[i];
+    const D x = f * w[i];
+    w[i] = x;
+    if (v32) {
+      v32[i] = lz_narrow<T>(x);
+      u[i] = T(0);
+    }
   }
 }
 
-template <typename T>
-void launch_lanczos_start(const Ctx& c, const T* v0, T* v, T* vp, double* norm, hipStream_t st) {
-  launch_k(k_lz_dot<T>, kLzParts, 256, 0, st, v0, v0, (int64_t)c.nd, c.d_red);
-  launch_k(k_lz_start<T>, kLzParts, 256, 0, st, v0, v, vp, (int64_t)c.nd, (const double*)c.d_red, norm);
+template <typename D, typename T>
+void launch_lanczos_start(const Ctx& c, const T* v0, const LanczosVec<D, T>& z, double* norm, hipStream_t st) {
+  launch_k(k_lz_norm<D, T>, kLzParts, 256, 0, st, v0, (int64_t)c.nd, c.d_red);
+  launch_k(k_lz_start<D, T>, kLzParts, 256, 0, st, v0, z.v, z.vp, z.v32, z.u, (int64_t)c.nd, (const double*)c.d_red,
+           norm);
 }
 
-// the step behind w = H v; carry: the last step's beta in, this one's out
-template <typename T>
-void launch_lanczos_step(const Ctx& c, T* v, T* vp, T* w, bool first, double* alpha, double* beta, double* carry,
-                         hipStream_t st) {
+// the step behind w (+ u) = H v, which leaves the next v and vp in z; carry:
+// the last step's beta in, this one's out
+template <typename D, typename T>
+void launch_lanczos_step(const Ctx& c, LanczosVec<D, T>& z, bool first, double* alpha, double* beta,
+                         double* carry, hipStream_t st) {
   const int64_t n = c.nd;
   double* const part2 = c.d_red + kLzParts;
-  launch_k(k_lz_dot<T>, kLzParts, 256, 0, st, (const T*)v, (const T*)w, n, c.d_red);
-  launch_k(k_lz_orth<T>, kLzParts, 256, 0, st, w, (const T*)v, (const T*)vp, n, (const double*)c.d_red, alpha,
-           first ? (const double*)nullptr : (const double*)carry, part2);
-  launch_k(k_lz_next<T>, kLzParts, 256, 0, st, v, vp, (const T*)w, n, (const double*)part2, beta, carry);
+  launch_k(k_lz_dot<D, T>, kLzParts, 256, 0, st, (const D*)z.v, (const D*)z.w, (const T*)z.u, n, c.d_red);
+  launch_k(k_lz_orth<D, T>, kLzParts, 256, 0, st, z.w, (const T*)z.u, (const D*)z.v, (const D*)z.vp, n,
+           (const double*)c.d_red, alpha, first ? (const double*)nullptr : (const double*)carry, part2);
+  launch_k(k_lz_next<D, T>, kLzParts, 256, 0, st, z.w, z.v32, z.u, n, (const double*)part2, beta, carry);
+  std::swap(z.vp, z.v);
+  std::swap(z.v, z.w);
 }
 
 // eigenvectors (double, or interleaved double complex) -> block precision
@@ -285,8 +332,10 @@ void launch_density(const Ctx& c, const T* X, int64_t ld, const double* occ, dou
 }
 
 #define INST(T)                                                                                        \
-  template void launch_lanczos_start<T>(const Ctx&, const T*, T*, T*, double*, hipStream_t);          \
-  template void launch_lanczos_step<T>(const Ctx&, T*, T*, T*, bool, double*, double*, double*, hipStream_t); \
+  template void launch_lanczos_start<double_of<T>, T>(const Ctx&, const T*, const LanczosVec<double_of<T>, T>&,   \
+                                                      double*, hipStream_t);                           \
+  template void launch_lanczos_step<double_of<T>, T>(const Ctx&, LanczosVec<double_of<T>, T>&, bool, double*, double*, \
+                                                     double*, hipStream_t);                            \
   template void launch_convert_c<T>(const double*, T*, int, int, hipStream_t);                         \
   template void launch_occupation_matrix<T>(const Ctx&, int, int, const T*, hipStream_t);              \
   template void launch_density<T>(const Ctx&, const T*, int64_t, const double*, double, double*, hipStream_t);

@@ -706,7 +706,9 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
   const int n1 = c.p.n[0], n2 = c.p.n[1], n3 = c.p.n[2];
   const int R = c.p.n0;
   StencilShape sh{c.tile_x, c.tile_yt, c.ry, c.tile_z, c.halo_ring};
-  if (sh.TX > 0 && shape_ok(c, sh, R)) return sh;
+  // (a tuned shape is one of the block's type; Lanczos vectors may be wider)
+  const bool own = elem == (c.mixed ? 4 : 8) * (c.any_complex ? 2 : 1);
+  if (own && sh.TX > 0 && shape_ok(c, sh, R)) return sh;
   sh.ring = 0;
   sh.TX = n1 <= 128 ? n1 : 64;
   auto tiles = [&] {

@@ -47,3 +47,31 @@ def test_lanczos_steps(precision, k):
         with pytest.raises(hcu.HcuError):
             ctx.lanczos_bounds(0, 0, 10)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,k", [((36, 36, 24), 0), ((31, 33, 20), 0), ((40, 28, 22), 0), ((36, 36, 24), 1)])
+def test_lowest_ritz_value_of_fp32_blocks(n, k):
+    """The lowest Ritz value of FP32 blocks against the FP64 oracle, 20 start
+    vectors: the vectors are doubles, so only the projector term rounds in 32
+    bits.  Its norm is at most the largest coupling, 1 Ha; the table, the
+    projections, the coupled projections and the result round it by at most
+    4e-7 of that together, which bounds the shift of a Ritz value in Ha."""
+    torch = _torch()
+    from oracle import chfsi
+    from oracle.hamiltonian import Hamiltonian
+    from paper_2507_23612_amd import hcu
+    cfg = workloads.make_config("c1")
+    cfg["n"] = np.array(n, np.int32)
+    if k:
+        cfg["kpts"] = np.array([[0.11, 0.05, -0.13]])
+    ctx = hcu.HcuContext(cfg, "mixed")
+    D = hcu.initial_occupation(ctx, cfg)
+    ctx.set_hubbard_occupation(D)
+    H = Hamiltonian(cfg, cfg["kpts"][0], D=list(D[0]))
+    X = torch.from_numpy(workloads.random_block(ctx.nd, max(20, ctx.ns), 11, bool(k))).cuda().to(ctx.dtype)
+    for i in range(20):
+        ctx.set_start(0, 0, X[:ctx.ns], X[i].clone())
+        got, b = ctx.lanczos_bounds(0, 0, 10)
+        want, wb = chfsi.lanczos(H.apply, X[i].cpu().numpy().astype(np.complex128 if k else np.float64), 10)
+        assert abs(got - want) < 4e-7 and abs(b - wb) < 4e-7, (i, got - want, b - wb)
+    ctx.close()
