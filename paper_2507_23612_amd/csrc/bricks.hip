@@ -82,6 +82,15 @@ template <typename T, bool SC> constexpr bool kDirect = !SC && sizeof(T) == 16;
 template <typename T, bool SC, bool PR>
 constexpr int kBrickLds = (2 * kChunkVals + (PR && !kDirect<T, SC> ? 4 * 16 * kTileRow<T> : 0)) * (int)sizeof(T);
 
+// A projection brick has up to 640 points, complex ones with two products
+// each.  In 32 bits one chain of additions over all of them rounds at the size
+// that its sum has reached, so each 64-point brick is summed from zero and
+// joins the total once; the sum over the projection bricks runs in double
+// precision (proj.hip).  Forces of 36 random blocks 0.9e-6 off 64 bits, complex
+// ones 1.2e-6 (one chain: 1.3e-6 and 1.7e-6), in the same time; 1e-15 is left
+// as it is in 64 bits, where this took 1 % of a complex filter.
+template <typename T> constexpr bool kPieceSums = sizeof(typename El<T>::R) == 4;
+
 // Waves per SIMD that the registers are allotted for: what the accumulators
 // (a brick's values, as many requested ahead, NT slot tiles) leave room for.
 // (FP64 with four tiles: two waves instead of three cost 0.72 instead of 0.65
@@ -350,20 +359,24 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
           if (wave_ok) {
             const E* __restrict__ w = ring + par * kChunkVals + lane * G;
             const E* __restrict__ y = yw + n * RS + G * q;
+            V sum[C];
+            for (int c = 0; c < C; ++c)
+              for (int r = 0; r < 4; ++r) sum[c][r] = kPieceSums<T> ? R(0) : pacc[t][c][r];
             for (int i = 0; i < NG; ++i) {
               const Pack<E> f = ld_pack(w + i * (64 * G));
               Pack<E> v;
               if constexpr (DIR) v.v[0] = value(i / 4, i % 4);
               else v = ld_pack(y + 4 * G * i);
               for (int e = 0; e < G; ++e) {
-                for (int c = 0; c < C; ++c)
-                  pacc[t][c] = Mf<R>::mfma(part_of(f.v[e], 0), part_of(v.v[e], c), pacc[t][c]);
+                for (int c = 0; c < C; ++c) sum[c] = Mf<R>::mfma(part_of(f.v[e], 0), part_of(v.v[e], c), sum[c]);
                 if constexpr (C == 2) {
-                  pacc[t][0] = Mf<R>::mfma(f.v[e].y, v.v[e].y, pacc[t][0]);
-                  pacc[t][1] = Mf<R>::mfma(-f.v[e].y, v.v[e].x, pacc[t][1]);
+                  sum[0] = Mf<R>::mfma(f.v[e].y, v.v[e].y, sum[0]);
+                  sum[1] = Mf<R>::mfma(-f.v[e].y, v.v[e].x, sum[1]);
                 }
               }
             }
+            for (int c = 0; c < C; ++c)
+              for (int r = 0; r < 4; ++r) pacc[t][c][r] = kPieceSums<T> ? pacc[t][c][r] + sum[c][r] : sum[c][r];
           }
           __builtin_amdgcn_sched_barrier(0);
           par ^= 1;

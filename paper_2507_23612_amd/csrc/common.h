@@ -49,6 +49,10 @@ template <typename R> __host__ __device__ inline cplx<R> mul_conj(cplx<R> a, cpl
 template <typename T> __host__ __device__ inline T make_scalar(double re, double im) { (void)im; return T(re); }
 template <> __host__ __device__ inline cplx<double> make_scalar<cplx<double>>(double re, double im) { return {re, im}; }
 template <> __host__ __device__ inline cplx<float> make_scalar<cplx<float>>(double re, double im) { return {float(re), float(im)}; }
+template <typename T> __host__ __device__ inline double_of<T> widen(T x) { return x; }
+template <> __host__ __device__ inline cplx<double> widen(cplx<float> x) { return {x.re, x.im}; }
+template <typename T> __host__ __device__ inline T narrow(double_of<T> x) { return (T)x; }
+template <> __host__ __device__ inline cplx<float> narrow<cplx<float>>(cplx<double> x) { return {float(x.re), float(x.im)}; }
 
 // ---------------------------------------------------------------- wave-private LDS hand-off
 // Lanes of one wave exchange values through LDS (one lane writes what another

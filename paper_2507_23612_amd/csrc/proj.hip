@@ -29,8 +29,9 @@ __global__ __launch_bounds__(1024) void k_slot_sum(const TailJob* __restrict__ j
                                                    T* __restrict__ P, int ldp, int ncol,
                                                    const int64_t* __restrict__ jrow, int nproj, double dv) {
   using RT = typename real_of<T>::type;
-  __shared__ __attribute__((aligned(16))) unsigned char red_raw[16 * 64 * sizeof(T)];
-  T(*red)[64] = reinterpret_cast<T(*)[64]>(red_raw);
+  using D = double_of<T>;
+  __shared__ __attribute__((aligned(16))) unsigned char red_raw[16 * 64 * sizeof(D)];
+  D(*red)[64] = reinterpret_cast<D(*)[64]>(red_raw);
   if constexpr (JOBS) {
     part = (const T*)jobs[blockIdx.z].part;
     P = (T*)jobs[blockIdx.z].P;
@@ -38,22 +39,22 @@ __global__ __launch_bounds__(1024) void k_slot_sum(const TailJob* __restrict__ j
   const int j = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int s = blockIdx.x * 64 + lane;
-  T x0 = T(0), x1 = T(0);
+  D x0 = D(0), x1 = D(0);
   if (s < ncol) {
     const int64_t r1 = jrow[j + 1];
     int64_t r = jrow[j] + wave;
     for (; r + 16 < r1; r += 32) {
-      x0 += part[r * ldp + s];
-      x1 += part[(r + 16) * ldp + s];
+      x0 += widen(part[r * ldp + s]);
+      x1 += widen(part[(r + 16) * ldp + s]);
     }
-    if (r < r1) x0 += part[r * ldp + s];
+    if (r < r1) x0 += widen(part[r * ldp + s]);
   }
   red[wave][lane] = x0 + x1;
   __syncthreads();
   if (wave == 0 && s < ncol) {
-    T x = T(0);
+    D x = D(0);
     for (int w = 0; w < 16; ++w) x += red[w][lane];
-    P[(int64_t)s * nproj + j] = (RT)dv * x;
+    P[(int64_t)s * nproj + j] = narrow<T>(dv * x);
   }
 }
 

@@ -42,17 +42,6 @@ constexpr int kLzParts = 256;
 
 __device__ inline double lz_re(double x) { return x; }
 __device__ inline double lz_re(cplx<double> x) { return x.re; }
-template <typename D, typename T>
-__device__ inline D lz_widen(T x) {
-  if constexpr (std::is_arithmetic<T>::value) return (D)x;
-  else return D((double)x.re, (double)x.im);
-}
-template <typename T, typename D>
-__device__ inline T lz_narrow(D x) {
-  if constexpr (std::is_arithmetic<T>::value) return (T)x;
-  else return T((typename real_of<T>::type)x.re, (typename real_of<T>::type)x.im);
-}
-
 // part[b] = workgroup b's share of Re sum conj(x) (y + u)
 template <typename D, typename T>
 __global__ __launch_bounds__(256) void k_lz_dot(const D* __restrict__ x, const D* __restrict__ y,
@@ -61,7 +50,7 @@ __global__ __launch_bounds__(256) void k_lz_dot(const D* __restrict__ x, const D
   double re = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
     D z = y[i];
-    if (u) z += lz_widen<D>(u[i]);
+    if (u) z += widen(u[i]);
     re += lz_re(mul_conj(z, x[i]));
   }
   re = block_sum(re, sh);
@@ -74,7 +63,7 @@ __global__ __launch_bounds__(256) void k_lz_norm(const T* __restrict__ x, int64_
   __shared__ double sh[256];
   double re = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
-    const D z = lz_widen<D>(x[i]);
+    const D z = widen(x[i]);
     re += lz_re(mul_conj(z, z));
   }
   re = block_sum(re, sh);
@@ -91,11 +80,11 @@ __global__ __launch_bounds__(256) void k_lz_start(const T* __restrict__ v0, D* _
   if (blockIdx.x == 0 && threadIdx.x == 0) *norm = nrm;
   const double f = 1.0 / nrm;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
-    const D x = f * lz_widen<D>(v0[i]);
+    const D x = f * widen(v0[i]);
     v[i] = x;
     vp[i] = D(0);
     if (v32) {
-      v32[i] = lz_narrow<T>(x);
+      v32[i] = narrow<T>(x);
       u[i] = T(0);
     }
   }
@@ -114,7 +103,7 @@ __global__ __launch_bounds__(256) void k_lz_orth(D* __restrict__ w, const T* __r
   double re = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * kLzParts) {
     D x = w[i];
-    if (u) x += lz_widen<D>(u[i]);
+    if (u) x += widen(u[i]);
     x += a * v[i];
     if (bprev) x += b * vp[i];
     w[i] = x;
@@ -138,7 +127,7 @@ __global__ __launch_bounds__(256) void k_lz_next(D* __restrict__ w, T* __restric
     const D x = f * w[i];
     w[i] = x;
     if (v32) {
-      v32[i] = lz_narrow<T>(x);
+      v32[i] = narrow<T>(x);
       u[i] = T(0);
     }
   }
