@@ -296,7 +296,7 @@ __device__ __forceinline__ void brick_pass(const BrickGeo& geo, const BrickArgs<
           } else if constexpr (!PR) {
             left -= ns;
             if (left > 0) {
-              if (ns == 1) jvn = ip[lane];   // (else loaded with the next brick's values)
+              if (ns == 1 || !fetch) jvn = ip[lane];   // (else loaded with the next brick's values)
               request_scatter(0);
             }
           } else {

@@ -102,3 +102,75 @@ def test_rounding_of_fp32_projections():
             c.close()
     forces, stress = np.exp(np.mean(np.log(rms), axis=0))
     assert forces < 1.20e-6 and stress < 1.29e-6, (forces, stress)
+
+
+def _chunks(H, points):
+    """Chunks of 16 functions that touch each brick; points [brick][64]."""
+    of = np.full(H.nd, -1)
+    for b, p in enumerate(points):
+        of[p] = b
+    count = np.zeros(len(points), int)
+    for a in H.atoms:
+        for idx, vals in ((a["kb_idx"], a["kb_vals"]), (a["hub_idx"], a["hub_vals"]) if "hub_idx" in a else ((), ())):
+            if len(idx):
+                count[np.unique(of[idx])] += len(vals)
+    return (count + 15) // 16
+
+
+@pytest.mark.parametrize("layout,precision,k", [("runs", "fp64", 0), ("runs", "mixed", 0), ("runs", "fp64", 1),
+                                                ("runs", "mixed", 1), ("stacks", "mixed", 0)])
+def test_scatter_alone_past_an_empty_brick(layout, precision, k):
+    """Enough states that the scatter alone takes whole groups of bricks, and in
+    a group a brick of more than 16 functions, then one that no function
+    touches, then one with functions again: its function list is the third
+    brick's.  runs: 64 points each, four to a row, atoms apart in x; stacks:
+    blocks of 16 x 4 points, two planes by five blocks in y, supports that meet
+    the first plane of a pair last and one block of rows of it each."""
+    torch = _torch()
+    from oracle import chfsi
+    from oracle.hamiltonian import Hamiltonian
+    from paper_2507_23612_amd import hcu
+    cfg = workloads.make_config("tiny")
+    if layout == "runs":
+        n, ns, h = (256, 17, 10), 420, 0.4
+        pos = [(12.6, 2.0, 1.0), (13.1, 4.0, 2.0), (64.0, 3.0, 2.0)]
+    else:
+        n, ns, h = (32, 40, 32), 1000, 0.5
+        pos = [(6.0 + 0.1 * i, 0.75, 3.7) for i in range(4)] + [(6.0, 2.75, 3.7)]
+    cfg.update(n=np.array(n, np.int32), ns=ns, nelec=1.0, L=h * np.array(n), pos=np.array(pos),
+               atom_species=np.zeros(len(pos), np.int32))
+    if k:
+        cfg["kpts"] = np.array([[0.02, 0.05, -0.13]])
+    H = Hamiltonian(cfg, cfg["kpts"][0] if k else (0.0, 0.0, 0.0))
+    grid = np.arange(H.nd).reshape(n[::-1])
+    if layout == "runs":
+        groups = grid.reshape(-1, 4, 64)
+    else:   # [z pair][x block][y stack] groups of [y block][plane] bricks
+        g = grid.reshape(16, 2, 2, 5, 4, 2, 16).transpose(0, 2, 5, 3, 1, 4, 6)
+        groups = g.reshape(-1, 10, 64)
+    c = _chunks(H, groups.reshape(-1, 64)).reshape(groups.shape[:2])
+    met = [(a, b) for a in range(c.shape[0]) for b in range(c.shape[1] - 2)
+           if c[a, b] >= 2 and c[a, b + 1] == 0 and c[a, b + 2:].any()]
+    assert met
+    ctx = hcu.HcuContext(cfg, precision)
+    rng = np.random.default_rng(3)
+    D = rng.normal(size=(1, ctx.nhub, 5, 5)) * 0.05
+    D = 0.2 * np.eye(5) + D + D.transpose(0, 1, 3, 2)
+    ctx.set_hubbard_occupation(D)
+    H.set_occupation(list(D[0]))
+    X = torch.from_numpy(workloads.random_block(ctx.nd, ns, 3, bool(k))).cuda().to(ctx.dtype)
+    cols = [0, 63, 64, 200, ns - 1]
+    Xh = X[cols].cpu().numpy().astype(np.complex128 if k else np.float64)
+    want = H.apply(Xh)
+    bounds = (4.0, 2.0 * float(np.abs(want).max()), -1.0)
+    filtered = chfsi.cheb_filter(H.apply, Xh, 3, *bounds)
+    Y = torch.empty_like(X)
+    fp64 = precision == "fp64"
+    for call, ref, tol in ((lambda: ctx.apply_h(X, Y), want, 1e-12 if fp64 else 2e-6),
+                           (lambda: ctx.cheb_filter(X, Y, 3, *bounds), filtered, 1e-11 if fp64 else 3e-5)):
+        Y.fill_(float("nan"))
+        call()
+        err = float(np.abs(Y[cols].cpu().numpy() - ref).max() / np.abs(ref).max())
+        print(f"[gpu] scatter past an empty brick {layout} {precision} k={k}: {err:.1e}", flush=True)
+        assert err < tol
+    ctx.close()
