@@ -449,7 +449,7 @@ struct BatchLaunch {
   unsigned long long total;     // work items
   int TX, TYt, RY, R;
   int vx;                       // points per vector
-  int halo_slots;               // most halo values per thread and plane over the jobs
+  int halo_slots;               // most halo vectors per thread and plane over the jobs
 };
 template <typename T>
 hcu_status plan_stencil_batch(const std::vector<StencilJob>& jobs, std::vector<unsigned char>& host,

@@ -16,6 +16,7 @@
 // z weights to the running sums of the 2R outputs around it, which wait in
 // registers (as many as a queue of z neighbours would take).
 #include "common.h"
+#include "stencil_tile.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -163,14 +164,6 @@ __device__ inline int wrap(int g, int n, int& w) {
   return g - w * n;
 }
 
-// Halo vectors a thread stages per plane (the host checks the bound in single
-// values, kHaloSlots): 8 slots of one point, 4 of two and 3 of four cover
-// every admitted shape; half as many serve most tiles, and each slot costs
-// registers.
-constexpr int kHaloSlots = 8;
-constexpr int kHaloSlotsSmall = 4;
-template <int VX, bool SMALL>
-constexpr int kSlots = VX == 4 ? (SMALL ? 1 : 3) : (SMALL ? kHaloSlotsSmall : kHaloSlots) / VX;
 constexpr int kRingR = 6;   // shapes with the halo_ring flag: order-12 stencil
 
 // Threads per workgroup a variant is built for: the light real ones (one
@@ -647,18 +640,6 @@ static bool big_ok(const Ctx& c, int RY) {
   return c.mixed ? RY <= 2 : RY == 1;
 }
 
-// halo values per thread and plane for a tile on a grid with n1 points in x
-static int halo_slots(int n1, int TX, int TYt, int TY, int R) {
-  const int nthr = TX * TYt;
-  const int nh = 2 * R * TX + ((TX == n1 && n1 >= R) ? 0 : TY * 2 * R);
-  return (nh + nthr - 1) / nthr;
-}
-
-// halo values of a plane for a tile on a grid with n1 points in x
-static int halo_values(int n1, int TX, int TY, int R) {
-  return 2 * R * TX + ((TX == n1 && n1 >= R) ? 0 : TY * 2 * R);
-}
-
 // LDS of a workgroup: two staged planes with halo (x margin in whole
 // vectors) and 16 spare bytes each
 static size_t stencil_lds(int TX, int TYt, int RY, int R, size_t elem, int vx) {
@@ -749,8 +730,7 @@ static void allow_lds(K kernel, size_t lds) {
 // The points of a thread (PT of them, a shape's ry) lie side by side in x
 // where the rows allow whole vectors, else stacked in y.  One vector access
 // then moves up to 16 bytes of LDS and memory per lane, and the x neighbours
-// of a vector overlap.  Built for the orders 8 and 12 (the halo slots count on x
-// margins of R rounded to whole vectors no further than that).
+// of a vector overlap.  Built for the orders 8 and 12.
 template <typename T>
 static int vector_points(int R, int PT, int n1, int TX) {
   if (!vectors_built(R)) return 1;
@@ -759,11 +739,12 @@ static int vector_points(int R, int PT, int n1, int TX) {
   return vx;
 }
 
-// f(points per vector, rows of vectors per thread, few halo slots) as constants
+// f(points per vector, rows of vectors per thread, few halo slots) as
+// constants, for nh halo vectors per thread and plane
 template <typename T, int R, typename F>
-static void for_variant(int PT, int vx, bool small, F f) {
+static void for_variant(int PT, int vx, int nh, F f) {
   auto slots = [&](auto v, auto ry) {
-    if (small) f(v, ry, std::true_type());
+    if (nh <= kSlots<decltype(v)::value, true>) f(v, ry, std::true_type());
     else f(v, ry, std::false_type());
   };
   using I1 = std::integral_constant<int, 1>;
@@ -810,13 +791,13 @@ static KArgs<RT> stencil_args(const Ctx& c, int ik, double alpha, double cshift,
 }
 
 template <typename T, typename RT, int R>
-static void launch_r(int RY, int vx, bool small_halo, const KArgs<RT>& a, dim3 grid, dim3 block, size_t lds, const T* Yin,
+static void launch_r(int RY, int vx, int nh, const KArgs<RT>& a, dim3 grid, dim3 block, size_t lds, const T* Yin,
                      const T* Yprev, T* Yout, const RT* V, hipStream_t st) {
   auto go = [&](auto kernel) {
     allow_lds(kernel, lds);
     launch_k(kernel, grid, block, lds, st, Yin, Yprev, Yout, V, a);
   };
-  for_variant<T, R>(RY, vx, small_halo, [&](auto v, auto ry, auto small) {
+  for_variant<T, R>(RY, vx, nh, [&](auto v, auto ry, auto small) {
     constexpr int VX = decltype(v)::value, NR = decltype(ry)::value;
     go(k_stencil<T, RT, R, VX, NR, kSlots<VX, decltype(small)::value>>);
   });
@@ -840,23 +821,23 @@ void launch_stencil(const Ctx& c, int ik, const T* Yin, int64_t ld, const T* Ypr
   const int vx = vector_points<T>(R, sh.RY, a.n1, TX);
   dim3 block(TX / vx, TYt * vx);
   const size_t lds = stencil_lds(TX, TYt, sh.RY, R, sizeof(T), vx);
-  const bool small = halo_slots(a.n1, TX, TYt, TY, R) <= kHaloSlotsSmall;
+  const int nh = halo_vectors(a.n1, TX, TYt, TY, R, vx);
   const RT* V;
   if constexpr (sizeof(RT) == 4) V = c.d_Vf; else V = c.d_V;
   switch (R) {
-    case 1: launch_r<T, RT, 1>(sh.RY, vx, small, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
-    case 2: launch_r<T, RT, 2>(sh.RY, vx, small, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
-    case 3: launch_r<T, RT, 3>(sh.RY, vx, small, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
-    case 4: launch_r<T, RT, 4>(sh.RY, vx, small, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
-    case 5: launch_r<T, RT, 5>(sh.RY, vx, small, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
-    default: launch_r<T, RT, 6>(sh.RY, vx, small, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
+    case 1: launch_r<T, RT, 1>(sh.RY, vx, nh, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
+    case 2: launch_r<T, RT, 2>(sh.RY, vx, nh, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
+    case 3: launch_r<T, RT, 3>(sh.RY, vx, nh, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
+    case 4: launch_r<T, RT, 4>(sh.RY, vx, nh, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
+    case 5: launch_r<T, RT, 5>(sh.RY, vx, nh, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
+    default: launch_r<T, RT, 6>(sh.RY, vx, nh, a, grid, block, lds, Yin, Yprev, Yout, V, st); break;
   }
 }
 
 template <typename T, typename RT, int R>
-static void launch_batch_r(int RY, int vx, bool small_halo, unsigned items, dim3 block, size_t lds,
+static void launch_batch_r(int RY, int vx, int nh, unsigned items, dim3 block, size_t lds,
                            const SJob<RT>* jobs, int njobs, hipStream_t st) {
-  for_variant<T, R>(RY, vx, small_halo, [&](auto v, auto ry, auto small) {
+  for_variant<T, R>(RY, vx, nh, [&](auto v, auto ry, auto small) {
     constexpr int VX = decltype(v)::value, NR = decltype(ry)::value;
     constexpr auto kernel = k_stencil_multi<T, RT, R, VX, NR, kSlots<VX, decltype(small)::value>>;
     allow_lds(kernel, lds);
@@ -938,7 +919,7 @@ hcu_status plan_stencil_batch(const std::vector<StencilJob>& jobs, std::vector<u
       if (gid[i] != (int)g) continue;
       const StencilJob& j = jobs[i];
       const Ctx& c = *j.c;
-      L.halo_slots = std::max(L.halo_slots, halo_slots(c.p.n[0], TX, TYt, TY, R));
+      L.halo_slots = std::max(L.halo_slots, halo_vectors(c.p.n[0], TX, TYt, TY, R, L.vx));
       KArgs<RT> a = stencil_args<RT>(c, j.ik, j.alpha, j.cshift, j.beta, j.Yprev != nullptr);
       a.ld = j.ld; a.ld_prev = j.ld_prev; a.ld_out = j.ld_out;
       a.tiles_x = (a.n1 + TX - 1) / TX;
@@ -965,17 +946,16 @@ template <typename T>
 hcu_status run_stencil_batch(const BatchLaunch& L, const void* d_jobs, hipStream_t st) {
   using RT = typename real_of<T>::type;
   const size_t lds = stencil_lds(L.TX, L.TYt, L.RY, L.R, sizeof(T), L.vx);
-  const bool small = L.halo_slots <= kHaloSlotsSmall;
   const dim3 block(L.TX / L.vx, L.TYt * L.vx);
   const unsigned n = (unsigned)L.total;
   const SJob<RT>* dj = reinterpret_cast<const SJob<RT>*>(d_jobs) + L.first;
   switch (L.R) {
-    case 1: launch_batch_r<T, RT, 1>(L.RY, L.vx, small, n, block, lds, dj, L.njob, st); break;
-    case 2: launch_batch_r<T, RT, 2>(L.RY, L.vx, small, n, block, lds, dj, L.njob, st); break;
-    case 3: launch_batch_r<T, RT, 3>(L.RY, L.vx, small, n, block, lds, dj, L.njob, st); break;
-    case 4: launch_batch_r<T, RT, 4>(L.RY, L.vx, small, n, block, lds, dj, L.njob, st); break;
-    case 5: launch_batch_r<T, RT, 5>(L.RY, L.vx, small, n, block, lds, dj, L.njob, st); break;
-    default: launch_batch_r<T, RT, 6>(L.RY, L.vx, small, n, block, lds, dj, L.njob, st); break;
+    case 1: launch_batch_r<T, RT, 1>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;
+    case 2: launch_batch_r<T, RT, 2>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;
+    case 3: launch_batch_r<T, RT, 3>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;
+    case 4: launch_batch_r<T, RT, 4>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;
+    case 5: launch_batch_r<T, RT, 5>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;
+    default: launch_batch_r<T, RT, 6>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;
   }
   return hipGetLastError() == hipSuccess ? HCU_OK : HCU_DEVICE;
 }

@@ -119,3 +119,23 @@ def test_stencil_fp32_error(n, k, n0):
     err = np.linalg.norm(Y.cpu().numpy() - want) / np.linalg.norm(want)
     ctx.close()
     assert err < 2.5e-8 * np.sqrt(n0 + 6), err
+
+
+@pytest.mark.parametrize("shape", [(48, 4, 4), (36, 5, 4), (24, 6, 4), (32, 5, 4), (20, 8, 4), (16, 12, 4), (16, 16, 4)])
+def test_stencil_halo_of_partial_rows(shape):
+    """FP32, order 12: tiles that do not span the row, whose halo takes more
+    vectors than threads although it has at most four values for each."""
+    torch = _torch()
+    from oracle.hamiltonian import Hamiltonian
+    from paper_2507_23612_amd import hcu
+    cfg = _bare((52, 64, 9), 3, 6, 0)
+    ctx = hcu.HcuContext(cfg, "mixed")
+    X = torch.from_numpy(workloads.random_block(ctx.nd, 3, 5, False)).cuda().to(ctx.dtype)
+    Y = torch.empty_like(X)
+    want = Hamiltonian(cfg, cfg["kpts"][0]).apply(X.cpu().numpy().astype(np.float64))
+    for tz in (9, 4):
+        ctx.set_tuning(*shape, tz)
+        Y.fill_(float("nan"))
+        ctx.apply_h(X, Y)
+        assert float(np.abs(Y.cpu().numpy() - want).max() / np.abs(want).max()) < 2e-6
+    ctx.close()
