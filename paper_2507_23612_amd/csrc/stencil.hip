@@ -610,12 +610,13 @@ __attribute__((amdgpu_waves_per_eu(kWaves<T, VX, RY>))) void k_stencil(const T* 
 // Form over a list of jobs (blocks of possibly different grids): one workgroup
 // per work item (job, tile, z chunk, state), XCD-contiguous item order, the
 // job found by bisection on the items' start indices; the hardware dispatcher
-// balances.
+// balances.  first: the launch's first item (run_stencil_batch).
 template <typename T, typename RT, int R, int VX, int RY, int NHS>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(kWaves<T, VX, RY>))) void k_stencil_multi(const SJob<RT>* __restrict__ jobs, int njobs) {
+__attribute__((amdgpu_waves_per_eu(kWaves<T, VX, RY>))) void k_stencil_multi(const SJob<RT>* __restrict__ jobs, int njobs,
+                                                                    unsigned long long first) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const unsigned long long item = xcd_linear();
+  const unsigned long long item = first + xcd_linear();
   int lo = 0, hi = njobs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) / 2;
@@ -834,14 +835,21 @@ void launch_stencil(const Ctx& c, int ik, const T* Yin, int64_t ld, const T* Ypr
   }
 }
 
+// Work items of one launch: a grid has fewer than 2^32 threads in x, and a
+// batch may have more items than that (small tuned tiles of single planes).  A
+// million workgroups keep the device busy for milliseconds, so a further
+// launch costs nothing.
+constexpr unsigned long long kLaunchItems = 1 << 20;
+
 template <typename T, typename RT, int R>
-static void launch_batch_r(int RY, int vx, int nh, unsigned items, dim3 block, size_t lds,
+static void launch_batch_r(int RY, int vx, int nh, unsigned long long items, dim3 block, size_t lds,
                            const SJob<RT>* jobs, int njobs, hipStream_t st) {
   for_variant<T, R>(RY, vx, nh, [&](auto v, auto ry, auto small) {
     constexpr int VX = decltype(v)::value, NR = decltype(ry)::value;
     constexpr auto kernel = k_stencil_multi<T, RT, R, VX, NR, kSlots<VX, decltype(small)::value>>;
     allow_lds(kernel, lds);
-    launch_k(kernel, dim3(items), block, lds, st, jobs, njobs);
+    for (unsigned long long i = 0; i < items; i += kLaunchItems)
+      launch_k(kernel, dim3((unsigned)std::min(items - i, kLaunchItems)), block, lds, st, jobs, njobs, i);
   });
 }
 
@@ -947,7 +955,7 @@ hcu_status run_stencil_batch(const BatchLaunch& L, const void* d_jobs, hipStream
   using RT = typename real_of<T>::type;
   const size_t lds = stencil_lds(L.TX, L.TYt, L.RY, L.R, sizeof(T), L.vx);
   const dim3 block(L.TX / L.vx, L.TYt * L.vx);
-  const unsigned n = (unsigned)L.total;
+  const unsigned long long n = L.total;
   const SJob<RT>* dj = reinterpret_cast<const SJob<RT>*>(d_jobs) + L.first;
   switch (L.R) {
     case 1: launch_batch_r<T, RT, 1>(L.RY, L.vx, L.halo_slots, n, block, lds, dj, L.njob, st); break;

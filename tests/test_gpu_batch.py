@@ -193,3 +193,28 @@ def test_multi_block_context_batched_pass_equals_per_block_passes(ring):
     print(f"[gpu] 16-block context batched vs per block: max |d lambda| {np.max(np.abs(la - lb)):.2e}", flush=True)
     np.testing.assert_allclose(la[:, :, :8], lb[:, :, :8], atol=1e-6)
     batch.close()
+
+
+def test_batched_pass_of_more_items_than_one_launch():
+    """Tiles of 4 x 4 points and single planes: two blocks of 260 states make
+    more work items than one stencil launch takes."""
+    _torch()
+    from paper_2507_23612_amd import hcu
+    cfg = workloads.make_config("tiny")
+    cfg.update(n=np.array([32, 32, 32], np.int32), n0=1, ns=260, degree=4, nspin=2)
+    a, b = _prepared(cfg, d_seed=7), _prepared(cfg, d_seed=7)
+    a.set_tuning(4, 4, 1, 1)
+    assert 8 * 8 * 32 * 2 * cfg["ns"] > 1 << 20
+    for c in (a, b):
+        for s in range(2):
+            c.lanczos_bounds(s, 0)
+    batch = hcu.HcuBatch([a])
+    batch.chfsi_pass()
+    for s in range(2):
+        b.chfsi_pass(s, 0)
+    a.update_occupations()
+    b.update_occupations()
+    np.testing.assert_allclose(a.get_eigenvalues(), b.get_eigenvalues(), atol=1e-9)
+    batch.close()
+    a.close()
+    b.close()
