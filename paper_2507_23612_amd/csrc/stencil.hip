@@ -460,8 +460,9 @@ __device__ __forceinline__ void stencil_item(const T* __restrict__ Yin, const T*
 // a register queue and one pass over the plane forms the sum.  Without vectors
 // the forward sum's LDS reads are one point each as well, and its second pass
 // over them costs more than the halo rows it finds in L2: 63x63x41, 192
-// states, 145 us (FP32) and 272 us (FP64) in the queue, 268 and 401 forwards;
-// with vectors (64x62x40) 76 and 152 us forwards, 111 and 206 in the queue.
+// states, order 12, 132 us (FP32) and 219 us (FP64) in the queue, 268 and 401
+// forwards; with vectors (64x62x40, order 8) 75 and 151 us forwards, 111 and
+// 206 in the queue.
 //
 // FP32 tiles of odd checkerboard parity sweep their z range R planes behind
 // the even ones (periodic in z), so that their own reads of a plane coincide
@@ -701,7 +702,7 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
   auto set_rows = [&](int ry) {
     sh.RY = ry;
     while (sh.RY > 1 && sh.RY > n2) sh.RY /= 2;
-    sh.TYt = std::max(1, std::min((queue && elem == 4 && sh.TX > 64 ? 512 : 256) / sh.TX, n2 / sh.RY));
+    sh.TYt = std::max(1, std::min((queue && sh.TX > 64 ? 512 : 256) / sh.TX, n2 / sh.RY));
     // few rows on a narrow grid: single rows keep enough threads for the halo
     if (halo_slots(n1, sh.TX, sh.TYt, sh.TYt * sh.RY, R) > kHaloSlots) {
       sh.RY = 1;
@@ -709,13 +710,23 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
     }
   };
   sh.tz = n3;
-  // (99x99x85, 608 states, FP32 in a queue: 2 rows of 4 points 1.95 ms, 5 rows
-  // 1.64; 63x63x41, FP64: 4 points 333 us, 2 points 257)
-  set_rows(elem > 8 ? 1 : vectors ? 4 : queue && elem == 4 ? 4 : 2);
+  // In a queue: five rows rather than two where a row takes most of 256
+  // threads (99x99x85, 304 states, order 12: FP32 919 against 1298 us, FP64
+  // 1795 against 2448); FP64 from order 8 on two points (63x63x41, 192 states,
+  // order 12, two halves in z: 4 points 244 us, 2 points 219), the shorter
+  // queues four (order 6: 202 us with 2, 192 with 4).
+  set_rows(elem > 8 ? 1 : vectors || (queue && (elem == 4 || R <= 3)) ? 4 : 2);
   if (tiles() * ncol < 512) {
     if (sh.RY > 2) set_rows(2);
     int zs = 1;
     while (tiles() * ncol * zs < 768 && n3 / (2 * zs) >= 3) zs *= 2;
+    sh.tz = (n3 + zs - 1) / zs;
+  } else if (queue && (elem == 8 || R == 1)) {
+    // eight workgroups per CU in chunks of at least 16 planes (63x63x41, 192
+    // states, FP64 order 12: 248 us without, 219 with; FP32 order 2: 121 and 90,
+    // higher orders lose: order 12 128 and 132)
+    int zs = 1;
+    while (tiles() * ncol * zs < 2048 && n3 / (2 * zs) >= 16) zs *= 2;
     sh.tz = (n3 + zs - 1) / zs;
   }
   while (!shape_ok(c, sh, R) && sh.TYt > 1) --sh.TYt;
