@@ -682,7 +682,11 @@ bool stencil_shape_ok(const Ctx& c, int TX, int TYt, int RY, int tz, int ring) {
 // 653 us); below two workgroups per CU it is split: shorter tiles first, then
 // z until there are three per CU (c1, 32 states: 10.3 us with 768 workgroups
 // of 3 planes, 34 us with 128 of 12).  Sixteen-byte values take one point per
-// thread (their sums fill the registers), rows without whole vectors two.
+// thread (their sums fill the registers), complex rows without whole vectors
+// two.  Real points without vectors have their own rule (the queue form).
+// Measured over 21 odd grids of 49 to 151 points, orders 2 to 12, FP32 and FP64,
+// 8 to 300 states: 0.86 of the time of four points, whole rows of 256 threads
+// and at least 2048 workgroups of 16 planes, at most 1.13.
 static constexpr bool vectors_built(int R) { return R == 4 || R == kMaxR; }
 
 static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
@@ -702,32 +706,45 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
   auto set_rows = [&](int ry) {
     sh.RY = ry;
     while (sh.RY > 1 && sh.RY > n2) sh.RY /= 2;
-    sh.TYt = std::max(1, std::min((queue && sh.TX > 64 ? 512 : 256) / sh.TX, n2 / sh.RY));
+    sh.TYt = std::max(1, std::min(256 / sh.TX, n2 / sh.RY));
     // few rows on a narrow grid: single rows keep enough threads for the halo
     if (halo_slots(n1, sh.TX, sh.TYt, sh.TYt * sh.RY, R) > kHaloSlots) {
       sh.RY = 1;
       sh.TYt = std::max(1, std::min(256 / sh.TX, n2));
     }
   };
-  sh.tz = n3;
-  // In a queue: five rows rather than two where a row takes most of 256
-  // threads (99x99x85, 304 states, order 12: FP32 919 against 1298 us, FP64
-  // 1795 against 2448); FP64 from order 8 on two points (63x63x41, 192 states,
-  // order 12, two halves in z: 4 points 244 us, 2 points 219), the shorter
-  // queues four (order 6: 202 us with 2, 192 with 4).
-  set_rows(elem > 8 ? 1 : vectors || (queue && (elem == 4 || R <= 3)) ? 4 : 2);
-  if (tiles() * ncol < 512) {
+  // halves in z until the launch has `want` workgroups, as long as chunks keep
+  // `planes` planes; the number of workgroups
+  auto split_z = [&](int64_t want, int planes) {
+    int zs = 1;
+    while (tiles() * ncol * zs < want && n3 / (2 * zs) >= planes) zs *= 2;
+    sh.tz = (n3 + zs - 1) / zs;
+    return tiles() * ncol * zs;
+  };
+  int64_t wgs = 0;
+  if (queue) {
+    // The queue's chunks read 2R planes more than their own, but eight
+    // workgroups per CU are worth that down to 16 planes (75x75x60, 200 states,
+    // FP32 order 12: 339 us whole, 292 in halves).  FP64 from order 8 on takes
+    // two points (63x63x41, 192 states, order 12: 4 points 244 us, 2 points
+    // 219), the shorter queues four (order 6: 202 us with 2, 192 with 4).
+    set_rows(elem == 8 && R >= 4 ? 2 : 4);
+    // Two rows of threads that leave a fifth of their waves' lanes idle give
+    // way to 512 threads in a launch that fills the chip (99x99x85, 304 states,
+    // order 12: FP32 1298 -> 919 us, FP64 2448 -> 1795).
+    const int rows = 512 / sh.TX;
+    if (sh.TX > 64 && sh.TYt <= 2 && 5 * sh.TX * sh.TYt < 4 * 64 * ((sh.TX * sh.TYt + 63) / 64) &&
+        tiles() * ncol >= 2048 && rows * sh.RY <= n2)
+      sh.TYt = rows;
+    wgs = split_z(2048, 16);
+  } else {
+    set_rows(elem > 8 ? 1 : vectors ? 4 : 2);
+    sh.tz = n3;
+    wgs = tiles() * ncol;
+  }
+  if (wgs < (queue ? 384 : 512)) {
     if (sh.RY > 2) set_rows(2);
-    int zs = 1;
-    while (tiles() * ncol * zs < 768 && n3 / (2 * zs) >= 3) zs *= 2;
-    sh.tz = (n3 + zs - 1) / zs;
-  } else if (queue && (elem == 8 || R == 1)) {
-    // eight workgroups per CU in chunks of at least 16 planes (63x63x41, 192
-    // states, FP64 order 12: 248 us without, 219 with; FP32 order 2: 121 and 90,
-    // higher orders lose: order 12 128 and 132)
-    int zs = 1;
-    while (tiles() * ncol * zs < 2048 && n3 / (2 * zs) >= 16) zs *= 2;
-    sh.tz = (n3 + zs - 1) / zs;
+    split_z(768, 3);
   }
   while (!shape_ok(c, sh, R) && sh.TYt > 1) --sh.TYt;
   return sh;
