@@ -738,9 +738,16 @@ static StencilShape pick_tiles(const Ctx& c, int64_t ncol, int elem) {
       sh.TYt = rows;
     wgs = split_z(2048, 16);
   } else {
+    // FP32 keeps four points, with no more rows of threads than its tiles
+    // need, and z is split first, down to six planes (order 12: 60x60x40, 96
+    // states, two points and whole z ranges 65 us, four points and halves 44;
+    // 50x46x33, 160 states, tiles of 20 rows 64 us, of 16 rows 55).
     set_rows(elem > 8 ? 1 : vectors ? 4 : 2);
-    sh.tz = n3;
-    wgs = tiles() * ncol;
+    if (elem == 4) {
+      const int TY = sh.TYt * sh.RY, ny = (n2 + TY - 1) / TY;
+      sh.TYt = (n2 + ny * sh.RY - 1) / (ny * sh.RY);
+    }
+    wgs = split_z(elem == 4 ? 768 : 0, 6);
   }
   if (wgs < (queue ? 384 : 512)) {
     if (sh.RY > 2) set_rows(2);
