@@ -528,12 +528,13 @@ __global__ __launch_bounds__(kTdThreads) void k_hetrd_small(zc* __restrict__ A, 
 // The whole generalized eigensolve Hs C = S C diag(lam) of a small block in
 // one workgroup, in LDS: Cholesky factor S = U^H U, A = U^-H Hs U^-1, cyclic
 // Jacobi rotations of A (n / 2 disjoint pairs at a time, every 2 x 2 block of
-// pairs updated by one thread), C = U^-1 Q.  One complex block of 32 states:
-// 0.18 ms; the library's chain took 1.1 ms in about 150 launches, more than
-// the host can issue when a pass has many small blocks (two spins and 8
-// k-points of the 6-atom cell: the SCF 82 -> 67 ms).  From 65 states on the
-// two matrices no longer fit the LDS and the rotations' 10 n^3 work in one
-// workgroup nears the chain's time.
+// pairs updated by one thread), C = U^-1 Q.  A block of 32 states takes 0.26 ms
+// (real) or 0.25 (complex), of 64 states 0.73 or 0.98; the library's chain, about
+// 150 launches, 0.84, 1.14, 1.66 and 2.20, and the host cannot issue it fast
+// enough when a pass has many small blocks (two spins and 8 k-points of the
+// 6-atom cell: the SCF 82 -> 67 ms).  From 65 states on the two matrices no
+// longer fit the LDS, and the rotations' 10 n^3 work in one workgroup nears the
+// chain's time.
 //
 // Pair (p, q), A_pq = r e^{i phi}: with theta = (A_qq - A_pp) / 2r,
 // t = sign(theta) / (|theta| + sqrt(theta^2 + 1)), c = 1 / sqrt(t^2 + 1),

@@ -107,6 +107,22 @@ def test_cheb_filter_c3_mixed_fused_sampled_columns(layout):
     assert err < FP32_BAR
 
 
+def test_cheb_filter_c3_mixed_runs_of_points():
+    """The same cell on 108x107x96 points: an odd n2 admits no blocks, so the
+    bricks are runs of 64 consecutive points, four to a projection brick (its
+    eight-slot-tile variant: up to 98 functions)."""
+    cfg = workloads.make_config("c3")
+    cfg["n"] = np.array([108, 107, 96], np.int32)
+    nd = int(np.prod(cfg["n"]))
+    print("[gpu] filter c3 mixed full block (640 states, runs of 64 points), oracle on 4 columns", flush=True)
+    X = np.random.default_rng(35).random((cfg["ns"], nd), dtype=np.float32) - np.float32(0.5)
+    err, sizes = _run(cfg, "mixed", X, [3, 200, 411, 637], 42)
+    print(f"[gpu] filter c3 mixed (runs of 64 points): rel err {err:.2e}, most functions per projection brick "
+          f"{sizes['max_brick_functions']}", flush=True)
+    assert 64 < sizes["max_brick_functions"] <= 128
+    assert err < FP32_BAR
+
+
 def test_cheb_filter_c2_complex_fp32_block_sampled_columns():
     """One Bloch block of the c2 cell at a k-point of the shifted 2x2x2 set,
     complex FP32 (the block type of the batched spin/k workload): the fused
