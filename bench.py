@@ -467,7 +467,7 @@ def measure(args, config, precision, hcu, torch, top):
     tile = tile_name(tuning)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
-                "traffic": measured_traffic("k_stencil", config, prec, tile, ("stencil.hip",)),
+                "traffic": measured_traffic("k_stencil", config, prec, tile, ("stencil.hip", "stencil_tile.h")),
                 "kernel": ("k_stencil_multi (all (spin, k) blocks)" if nsk > 1 else "k_stencil")
                           + " (12th-order FD stencil + V_loc + Chebyshev three-term step)",
                 "avg_launch_ms": round(st_ms, 4), "algorithmic_bytes_per_launch": int(bytes_launch),

@@ -38,8 +38,8 @@ FLAGS = [
 # (source, object, extra flags); the stencil is compiled once per element type
 SOURCES = [("stencil.hip", f"stencil_{t}", [f"-DHCU_STENCIL_ELEM={i}"])
            for i, t in enumerate(("f64", "f32", "c128", "c64"))]
-SOURCES += [(f"{s}.hip", s, []) for s in ("setup", "nonlocal", "proj", "bricks", "gemm", "scf_kernels", "mlp", "state", "noalloc",
-                                          "forces", "hxc", "eig", "api")]
+SOURCES += [(f"{s}.hip", s, []) for s in ("setup", "proj", "bricks", "gemm", "scf_kernels", "mlp", "state", "noalloc", "forces",
+                                          "hxc", "eig", "api")]
 
 
 def _compile(unit, sanitize=False):

@@ -2,7 +2,7 @@
 // coupled projections, the projections of the result, or both at once,
 //   Y_b += alpha Phi_b Q                              (64-point bricks)
 //   part[pdest[slot]][s] = sum_{p in B} conj(Phi[slot][p]) Y[s][p]
-//                                          (projection bricks B of four bricks)
+//                                  (projection bricks B of four or ten bricks)
 // (Sec. II.A potential section and Sec. II.B: the Hubbard orbitals are
 // handled like nonlocal projectors).  Inside a Chebyshev step both run on the
 // step's output: the projections are those of the next step's input.
@@ -497,9 +497,15 @@ template void launch_brick_pass_batch<double>(const FusedJob*, int, unsigned, in
 template void launch_brick_pass_batch<float>(const FusedJob*, int, unsigned, int, int64_t, hipStream_t);
 template void launch_brick_pass_batch<cplx<float>>(const FusedJob*, int, unsigned, int, int64_t, hipStream_t);
 
+template <typename T>
+void launch_nl_scatter(const Ctx& c, int ik, T* Y, int64_t ld, int ncol, const T* Qt, double alpha, hipStream_t st) {
+  if (c.nproj > 0) launch_brick_pass<T>(c, (const T*)c.d_bval[ik], nullptr, Y, ld, ncol, Qt, alpha, true, false, st);
+}
+
 #define INST_BRICK(T)                                                                                             \
   template void launch_brick_pass<T>(const Ctx&, const T*, const T*, T*, int64_t, int, const T*, double, bool, bool, \
-                                     hipStream_t);
+                                     hipStream_t);                                                                \
+  template void launch_nl_scatter<T>(const Ctx&, int, T*, int64_t, int, const T*, double, hipStream_t);
 INST_BRICK(double)
 INST_BRICK(float)
 INST_BRICK(cplx<double>)

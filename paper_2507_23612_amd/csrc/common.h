@@ -456,7 +456,7 @@ hcu_status plan_stencil_batch(const std::vector<StencilJob>& jobs, std::vector<u
                               std::vector<BatchLaunch>& out);
 template <typename T>
 hcu_status run_stencil_batch(const BatchLaunch& L, const void* d_jobs, hipStream_t st);
-// nonlocal.hip: Y += alpha * sum_j phi_j Qt[j][s]  (64-point bricks on the
+// bricks.hip: Y += alpha * sum_j phi_j Qt[j][s]  (64-point bricks on the
 // matrix cores)
 template <typename T>
 void launch_nl_scatter(const Ctx& c, int ik, T* Y, int64_t ld, int ncol, const T* Qt, double alpha, hipStream_t st);

@@ -6,7 +6,7 @@
 // periodic wrap and the Bloch factor e^{+-i k_a L_a} on wrapped values
 // (Sec. II.B: off-grid indices are mapped back periodically with the Bloch
 // factor).  The projector term alpha * sum_j phi_j Q_j is added afterwards by
-// the state-blocked scatter kernel (nonlocal.hip).
+// the projector pass (bricks.hip).
 //
 // Layout: y is one column of an nd x ncol column-major block, x fastest.  A
 // workgroup owns a TX x TY tile of an x-y plane for one state and streams a
