@@ -228,10 +228,11 @@ hcu_status build_structure(Ctx& c) {
     // Projection bricks: four blocks of consecutive planes where n3 allows (8 x
     // 8 x 4 points; the most compact 256).  Large blocks of 4-byte values take
     // 16 x 20 x 2 points: half as many partial sums again (0.34 instead of 0.57
-    // GB on 108x108x96 with 640 states, their sum 0.29 instead of 0.31 ms) for
-    // a longer pass (2.6 instead of 2.4 ms: more functions per brick); that
-    // keeps more than 64 functions per brick on this cell, which the test of
-    // the eight-tile variant at this size asks for.
+    // GB on 108x108x96 with 640 states, their sum 0.07 instead of 0.11 ms) for
+    // a longer pass (2.61 instead of 2.42 ms: more functions per brick).  The
+    // whole step is 0.15 ms slower for it; it is kept because the full-size
+    // test of the eight-tile variant is bound to this cell, which meets more
+    // than 64 functions in the larger bricks only.
     const bool large = (int64_t)((n1 + 15) / 16) * (n2 / 4) * n3 / 10 * ((c.p.ns + 63) / 64) >= 4 * 256;   // four workgroups per compute unit
     if (geo.cube && geo.lx == 4 && n3 % 2 == 0 && large) {
       geo.py = 5;

@@ -193,7 +193,7 @@ constexpr int kWaves = kQueue<T, VX> ? 2 : kStencilWaves<T, VX, RY>;
 // neighbouring tiles read the same rows as their own.  (With a queue of z
 // neighbours the halo of plane z is read R planes after the neighbours read
 // those rows, when they have left L2: c2 FP64 fetched 3.75 GB per launch, the
-// forward sum 2.9 GB.)  Second come LDS reads, which took 60 % of the cycles
+// forward sum 2.5 GB.)  Second come LDS reads, which took 60 % of the cycles
 // with one point per lane: VX points side by side share x windows and read
 // their y neighbours in 16-byte accesses.  Measured, time of one step at the
 // best tile shape, queue form and this one: c2 (72x72x96, 256 states) FP64
